@@ -32,7 +32,7 @@
 // fill the tail.  Below 512k tokens a persistent grid pulls units from one list
 // per KV group, and the K/V tiles of a group stay in the caches of the XCDs that
 // serve it; rows much longer than the layer's work per workgroup are split into
-// chunks whose partial results attn_combine merges.  From 512k tokens on, rows
+// chunks, merged within the same launch.  From 512k tokens on, rows
 // are long enough that the workgroups of a persistent grid drift apart along the
 // key axis (the two workgroups sharing a CU do not advance at the same rate, and
 // each keeps its place for the whole layer), so concurrent readers of a K/V tile
@@ -72,7 +72,10 @@ constexpr float kSumLimit = 256.0f;          // a lane's tile sum of P above thi
 constexpr int kCostBuckets = 8192;
 constexpr int kOneShotMinLen = 1 << 19;  // from this length on, sparse lists run one unit per workgroup
 constexpr int kStaticListMaxLen = 8192;  // up to this length too, from one list by workgroup index (no atomics)
-constexpr int kMinChunk = 8;             // shortest chunk of a split row, in list entries
+// Shortest chunk of a split row, in list entries: shorter ones cost more in partial results
+// (66 KB each way) than the shorter critical path saves (attention at 4k tokens, 8 heads:
+// 56 us, at 6 entries 65 us; 2k tokens, 8 heads: 37.6 and 39.3 us).
+constexpr int kMinChunk = 8;
 constexpr int kItemUnitBits = 21;        // work item = unit | chunk << 21
 
 struct AttnArgs {
@@ -88,7 +91,7 @@ struct AttnArgs {
   int one_shot;          // 1: one unit per workgroup, all units in one queue
   int static_list;       // 1: all units in queue 0, workgroup i takes items i, i + grid, ...
   int* slot_base;        // split rows: first partial slot of the row's chunks, else -1
-  int* split_rows;       // the split rows (any order)
+  int* arrived;          // split rows: a 16-bit counter per slot (pairs of chunks merged)
   float* parts;          // partial results per slot: O[BQ][128], m[BQ], l[BQ] (fp32)
   int split_slots;       // partial slots available (0: rows are never split)
   int grid;              // workgroups of the persistent grid
@@ -318,13 +321,31 @@ __device__ __forceinline__ void pv_tile(int vbuf, const Offsets& off, const bf16
     }
 }
 
+// Partial results of split rows are exchanged between workgroups of one launch, which may
+// run on XCDs with L2 caches of their own: their loads and stores carry sc1 (agent scope),
+// so a store has reached the level that all XCDs share once its wave has waited for it,
+// and a load reads that level.
+constexpr int kAgentScope = 16;  // cache policy bit sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(const AttnArgs& a, int slot_floats) {
+  return __builtin_amdgcn_make_buffer_rsrc(a.parts, 0, a.split_slots * slot_floats * 4, 0x00020000);
+}
+
 // One (head, query block) unit, or one chunk of a split row's list: entries
-// [chunk * csize, chunk * csize + csize) when part is given, whose unnormalised
-// O, row max and row sum then go to the partial slot part instead of o.
+// [chunk * csize, chunk * csize + csize) when slot0 >= 0.  The chunks of a row are merged
+// pairwise in a fixed tree over the chunk index: of two siblings, the one that ends first
+// leaves its unnormalised O, row max and row sum in its slot and is done; the other merges
+// them with its own, still in registers (O = w_a O_a + w_b O_b, l alike, w_x = 2^((m_x - M) c),
+// M the larger max; a chunk whose keys are all masked has m = -inf and weighs nothing), and
+// goes on up the tree.  The result does not depend on which of the two that is, and no
+// workgroup ever waits for another.  A merge kernel after this one, which the host (not
+// knowing whether a row is split) launched for every layer, took 4.6 us without and 7.2 us
+// with split rows, and its cost had kept chunks long: attention at 4k tokens and 2 heads
+// 58.7 -> 46.0 us, at 24k tokens, 8 heads and 64-row blocks 703 -> 583 us (one workgroup
+// merging all chunks of a row in turn: 50 and 612 us).  flag: an int in LDS.
 template <int BQ, bool DENSE>
 __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, int lds0, const Offsets& off,
                                           const Fetch<Geo<BQ>::kWaves>& fe, int tid, int chunk = 0, int csize = 0,
-                                          float* part = nullptr) {
+                                          int slot0 = -1, int* flag = nullptr) {
   constexpr int QH = Geo<BQ>::kQH;
   constexpr int NW = Geo<BQ>::kWaves;
   constexpr int BK = Tile<BQ>::kBK, NMB = Tile<BQ>::kNMB;
@@ -338,7 +359,7 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
   const i32x4 rk = tensor_rsrc(a.k + (size_t)g * a.n * kHeadDim, a.n);
   const i32x4 rv = tensor_rsrc(a.v + (size_t)g * a.n * kHeadDim, a.n);
 
-  int beg = 0, cnt;
+  int beg = 0, cnt, nchunks = 0;
   const int32_t* cols = nullptr;
   if (DENSE) {
     cnt = qb + 1;
@@ -351,8 +372,9 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
     beg = (int)b0;
     cnt = (int)(e0 - b0);
     cols = a.col_idx + (size_t)head * cap;
-    if (part != nullptr) {
+    if (slot0 >= 0) {
       const int lo = chunk * csize;
+      nchunks = (cnt + csize - 1) / csize;
       beg += lo;
       cnt = cnt - lo < csize ? cnt - lo : csize;
     }
@@ -552,32 +574,72 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
     }
   }
 
-  if (!DENSE && part != nullptr) {
-    // partial result of one chunk: O unnormalised, the row max (of raw scores) and sum
+  float l_tot[QH];
 #pragma unroll
-    for (int h = 0; h < QH; ++h) {
-      const float l_tot = half_sum(l_run[h]);
-      const int r = qabs[h] - q0;
-      float* po = part + (size_t)r * kHeadDim;
+  for (int h = 0; h < QH; ++h) l_tot[h] = half_sum(l_run[h]);
+  if (!DENSE && slot0 >= 0) {
+    static_assert(QH == 1, "one half per wave");
+    constexpr int kSlotFloats = BQ * (kHeadDim + 2);
+    const __amdgpu_buffer_rsrc_t pr = parts_rsrc(a, kSlotFloats);
+    const int r = qabs[0] - q0;
+    const int row = 4 * (r * kHeadDim + 4 * (l >> 5)), stat = 4 * (BQ * kHeadDim + r);  // byte offsets in a slot
+    // node i of `count` at a level of the tree covers the chunks from i << level on
+    for (int i = chunk, count = nchunks, level = 0; count > 1; i >>= 1, count = (count + 1) >> 1, ++level) {
+      if ((i ^ 1) >= count) continue;  // no sibling: up as it is
+      const int node = slot0 + ((i | 1) << level);  // the pair's counter: 16 bits, at the right one's first slot
+      const int sh = 16 * (node & 1);
+      if (tid == 0)
+        *flag = (__hip_atomic_load(a.arrived + node / 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> sh) & 0xffff;
+      __syncthreads();
+      bool second = *flag != 0;
+      if (!second) {
+        const int own = (slot0 + (i << level)) * kSlotFloats * 4;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < 4; ++db)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int d = 32 * db + 8 * i4 + 4 * (l >> 5);
-          *reinterpret_cast<float4*>(po + d) =
-              make_float4(o[h][db][4 * i4], o[h][db][4 * i4 + 1], o[h][db][4 * i4 + 2], o[h][db][4 * i4 + 3]);
+          for (int i4 = 0; i4 < 4; ++i4) {
+            const f32x4 x = {o[0][db][4 * i4], o[0][db][4 * i4 + 1], o[0][db][4 * i4 + 2], o[0][db][4 * i4 + 3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), pr, row + 4 * (32 * db + 8 * i4), own,
+                                                   kAgentScope);
+          }
+        if ((l >> 5) == 0) {
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_run[0]), pr, stat, own, kAgentScope);
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(l_tot[0]), pr, stat + 4 * BQ, own, kAgentScope);
         }
-      if ((l >> 5) == 0) {
-        part[BQ * kHeadDim + r] = m_run[h];
-        part[BQ * kHeadDim + BQ + r] = l_tot;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have reached the shared level
+        __syncthreads();
+        if (tid == 0) *flag = (atomicAdd(a.arrived + node / 2, 1 << sh) >> sh) & 0xffff;
+        __syncthreads();
+        second = *flag != 0;
+        if (!second) return;
       }
+      const int sib = (slot0 + ((i ^ 1) << level)) * kSlotFloats * 4;
+      f32x4 y[16];
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        y[x] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pr, row + 4 * (32 * (x >> 2) + 8 * (x & 3)),
+                                                                               sib, kAgentScope));
+      const float ms = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, stat, sib, kAgentScope));
+      const float ls = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, stat + 4 * BQ, sib, kAgentScope));
+      const float M = fmaxf(m_run[0], ms);
+      const float wo = m_run[0] == -__builtin_inff() ? 0.f : fast_exp2((m_run[0] - M) * a.c);
+      const float ws = ms == -__builtin_inff() ? 0.f : fast_exp2((ms - M) * a.c);
+      // left w_left + right w_right, rounded the same whichever of the two merges
+      auto merged = [&](float own, float other) {
+        return i & 1 ? __builtin_fmaf(ws, other, wo * own) : __builtin_fmaf(wo, own, ws * other);
+      };
+      l_tot[0] = merged(l_tot[0], ls);
+      m_run[0] = M;
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[0][x >> 2][4 * (x & 3) + e] = merged(o[0][x >> 2][4 * (x & 3) + e], y[x][e]);
+      __syncthreads();  // every wave has read the flag
     }
-    return;
   }
 #pragma unroll
   for (int h = 0; h < QH; ++h) {
-    const float l_tot = half_sum(l_run[h]);
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float inv = l_tot[h] > 0.f ? 1.f / l_tot[h] : 0.f;
     if (qabs[h] < a.n) {
       uint16_t* orow = a.o + ((size_t)head * a.n + qabs[h]) * kHeadDim;
 #pragma unroll
@@ -623,7 +685,6 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
   const int x0 = home_queue(a, blockIdx.x % kNumXcd);
   const int* start = a.counter + 8;
   const int csize = a.counter[17];  // chunk length of split rows
-  constexpr size_t kSlotFloats = (size_t)BQ * (kHeadDim + 2);
   // Queues this workgroup has seen run dry (thread 0): they are never tried again.
   // A queue whose counter already reads past its end is skipped without an atomic
   // (a stale read only costs an extra atomic: counters never decrease).
@@ -659,19 +720,15 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
       *s_unit = unit;
     }
     __syncthreads();
-    const int item = *s_unit;
+    const int item = __builtin_amdgcn_readfirstlane(*s_unit);
     if (item < 0) break;
     // items carry a chunk index only when rows may be split (fewer than 2^21 units);
     // otherwise an item is the unit itself, which may exceed 2^21
     const bool split = a.split_slots > 0;
     const int unit = split ? item & ((1 << kItemUnitBits) - 1) : item;
     const int chunk = split ? item >> kItemUnitBits : 0;
-    float* part = nullptr;
-    if (a.split_slots > 0) {
-      const int sb = a.slot_base[unit];
-      if (sb >= 0) part = a.parts + (size_t)(sb + chunk) * kSlotFloats;
-    }
-    attn_unit<BQ, DENSE>(a, unit / a.nb, unit % a.nb, lds0, off, fe, tid, chunk, csize, part);
+    const int slot0 = split ? a.slot_base[unit] : -1;
+    attn_unit<BQ, DENSE>(a, unit / a.nb, unit % a.nb, lds0, off, fe, tid, chunk, csize, slot0, s_unit);
     if (a.one_shot) break;
   }
 #endif  // __HIP_DEVICE_COMPILE__
@@ -695,15 +752,17 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
 // time.  With G' = min(grid, slots / 2) and T the total of all rows' entries,
 // rows longer than C = max(ceil(T / G'), 8, ceil(N_b / 1024)) are cut into
 // ceil(L / C) chunks, each a work item of its own that leaves a partial result
-// in a slot; attn_combine merges them.  Chunks number at most T / C + (rows
-// longer than C) <= 2 G' <= slots.  The decision depends only on the lists and
-// the grid, so results do not depend on timing.
+// in a slot or merges its sibling's (attn_unit).  Chunks number at most
+// T / C + (rows longer than C) <= 2 G' <= slots.  When that bound on the slots and not
+// the grid sets C (few units), the C of the whole grid is tried first and taken if its
+// chunks fit the slots.  The decision depends only on the lists and the grid, so results
+// do not depend on timing.
 //
-// One workgroup builds everything and resets the queue counters; the order
+// One workgroup builds everything and resets the queue and arrival counters; the order
 // within one length is arbitrary (it only decides which workgroup runs an item,
 // never a result).  Schedule area: int counters[8], int start[9], int C (at 17,
-// INT_MAX when no row is split), int split rows (at 18); items from int offset
-// 64; then slot_base[units], split_rows[slots / 2] and the partial slots.
+// INT_MAX when no row is split); items from int offset 64; then slot_base[units],
+// arrived[slots / 2] and the partial slots.
 constexpr int kQueueBuckets = kCostBuckets / kNumXcd;  // 1024 cost buckets per queue
 
 __device__ __forceinline__ int cost_bucket(int64_t c) {
@@ -737,7 +796,7 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
   __shared__ int hist[kCostBuckets];
   __shared__ int part[1024];
   __shared__ unsigned long long s_tot;
-  __shared__ int s_max, s_slots, s_split;
+  __shared__ int s_max, s_slots, s_fit;
   const int tid = threadIdx.x;
   const int total = a.hq * a.nb;
   for (int i = tid; i < kCostBuckets; i += 1024) hist[i] = 0;
@@ -745,8 +804,9 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
     s_tot = 0ull;
     s_max = 0;
     s_slots = 0;
-    s_split = 0;
+    s_fit = 0;
   }
+  for (int i = tid; i < a.split_slots / 2; i += 1024) a.arrived[i] = 0;
   // Layers of up to 8192 units read each row length once, into registers, for all
   // three passes below (one memory latency instead of three on short layers).
   constexpr int kCached = 8;
@@ -791,13 +851,25 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
       atomicMax(&s_max, mx);
     }
     __syncthreads();
+    auto chunk_for = [&](long long g) {
+      long long c = (long long)((s_tot + (unsigned long long)g - 1) / (unsigned long long)g);
+      c = c > kMinChunk ? c : kMinChunk;
+      const long long cmin = (a.nb + 1023) / 1024;
+      return c > cmin ? c : cmin;
+    };
     long long gp = a.split_slots / 2;
     gp = a.grid < gp ? a.grid : gp;
     gp = gp < 1 ? 1 : gp;
-    long long c = (long long)((s_tot + (unsigned long long)gp - 1) / (unsigned long long)gp);
-    c = c > kMinChunk ? c : kMinChunk;
-    const long long cmin = (a.nb + 1023) / 1024;
-    c = c > cmin ? c : cmin;
+    long long c = chunk_for(gp);
+    const int cg = (int)chunk_for(a.grid);
+    if (cg < c && s_max > cg) {
+      int chunks = 0;
+      each_unit([&](int, int L) { chunks += L > cg ? (L + cg - 1) / cg : 0; });
+      chunks = wave_sum_i(chunks);
+      if ((tid & 63) == 0) atomicAdd(&s_fit, chunks);
+      __syncthreads();
+      if (s_fit <= a.split_slots) c = cg;
+    }
     if (s_max > c) C = (int)c;
   }
   auto key = [&](int h, int len) {
@@ -809,7 +881,6 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
       const int k = (L + C - 1) / C;
       for (int c = 0; c < k; ++c) atomicAdd(&hist[key(h, L - c * C < C ? L - c * C : C)], 1);
       a.slot_base[u] = atomicAdd(&s_slots, k);
-      a.split_rows[atomicAdd(&s_split, 1)] = u;
     } else {
       atomicAdd(&hist[key(h, L)], 1);
       if (a.split_slots > 0) a.slot_base[u] = -1;
@@ -859,7 +930,6 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
   if (tid == 0) {
     a.counter[8 + kNumXcd] = n_items;
     a.counter[17] = C;
-    a.counter[18] = s_split;
   }
   __syncthreads();
   each_unit([&](int u, int L) {
@@ -875,80 +945,6 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
       const_cast<int32_t*>(a.order)[pos] = u;
     }
   });
-}
-
-// Merges the chunks of each split row in chunk order:
-//   O = sum_c w_c O_c / sum_c w_c l_c,  w_c = 2^((m_c - M) c),  M = max_c m_c
-// (chunks whose keys are all masked have m_c = -inf and weigh nothing).  grid
-// slots / 2 (workgroups past the number of split rows exit), kCombineThreads threads:
-// BQ query rows x kCombineThreads / BQ lanes, each lane 128 BQ / kCombineThreads dims.
-// The chunks' row statistics and partial rows are loaded kCombineBatch chunks at a
-// time (one memory latency per batch, not per chunk) and summed in chunk order.
-constexpr int kCombineThreads = 1024, kCombineBatch = 4;
-template <int BQ>
-__global__ __launch_bounds__(kCombineThreads) void attn_combine(AttnArgs a) {
-  const int i = blockIdx.x;
-  if (i >= a.counter[18]) return;
-  const int C = a.counter[17];
-  const int u = a.split_rows[i];
-  const int head = u / a.nb, qb = u % a.nb;
-  const int k = (row_len(a, head, qb) + C - 1) / C;
-  constexpr int TPR = kCombineThreads / BQ, DPT = kHeadDim / TPR, NB = kCombineBatch;
-  constexpr size_t kSlotFloats = (size_t)BQ * (kHeadDim + 2);
-  const int r = threadIdx.x / TPR, d0 = (threadIdx.x % TPR) * DPT;
-  const float* base = a.parts + (size_t)a.slot_base[u] * kSlotFloats;
-  float M = -__builtin_inff();
-  for (int c0 = 0; c0 < k; c0 += NB) {
-    float mv[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      mv[j] = c0 + j < k ? base[(c0 + j) * kSlotFloats + BQ * kHeadDim + r] : -__builtin_inff();
-#pragma unroll
-    for (int j = 0; j < NB; ++j) M = fmaxf(M, mv[j]);
-  }
-  float acc[DPT];
-#pragma unroll
-  for (int e = 0; e < DPT; ++e) acc[e] = 0.f;
-  float lsum = 0.f;
-  for (int c0 = 0; c0 < k; c0 += NB) {
-    float mv[NB], lv[NB];
-    float4 pv[NB][DPT / 4];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const bool in = c0 + j < k;
-      const float* sl = base + (size_t)(in ? c0 + j : 0) * kSlotFloats;
-      mv[j] = in ? sl[BQ * kHeadDim + r] : -__builtin_inff();
-      lv[j] = in ? sl[BQ * kHeadDim + BQ + r] : 0.f;
-      const float4* po = reinterpret_cast<const float4*>(sl + (size_t)r * kHeadDim + d0);
-#pragma unroll
-      for (int e = 0; e < DPT / 4; ++e) pv[j][e] = in ? po[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (mv[j] == -__builtin_inff()) continue;  // also every slot past the last chunk
-      const float w = fast_exp2((mv[j] - M) * a.c);
-      lsum += w * lv[j];
-#pragma unroll
-      for (int e = 0; e < DPT / 4; ++e) {
-        acc[4 * e] += w * pv[j][e].x;
-        acc[4 * e + 1] += w * pv[j][e].y;
-        acc[4 * e + 2] += w * pv[j][e].z;
-        acc[4 * e + 3] += w * pv[j][e].w;
-      }
-    }
-  }
-  const int q = qb * BQ + r;
-  if (q >= a.n) return;
-  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-  uint16_t* orow = a.o + ((size_t)head * a.n + q) * kHeadDim + d0;
-#pragma unroll
-  for (int e = 0; e < DPT / 4; ++e) {
-    const bf16x2 lo = pack_bf16(acc[4 * e] * inv, acc[4 * e + 1] * inv);
-    const bf16x2 hi = pack_bf16(acc[4 * e + 2] * inv, acc[4 * e + 3] * inv);
-    bf16x4 v4;
-    v4[0] = lo[0]; v4[1] = lo[1]; v4[2] = hi[0]; v4[3] = hi[1];
-    *reinterpret_cast<bf16x4*>(orow + 4 * e) = v4;
-  }
 }
 
 template <int BQ, bool DENSE>
@@ -977,11 +973,11 @@ int persistent_grid() {
 }  // namespace
 
 // Schedule area of the sparse kernel: header and items, then (when rows may be
-// split: persistent mode, fewer than 2^21 units) slot_base, split_rows and the
+// split: below 512k tokens, fewer than 2^21 units) slot_base, arrived and the
 // partial slots.  Slots: min(max_slots, 2 x units).
 struct SchedLayout {
   int slots;
-  size_t slot_base, split_rows, parts, total;
+  size_t slot_base, arrived, parts, total;
 };
 
 SchedLayout sched_layout(const Dims& d, int max_slots) {
@@ -992,7 +988,7 @@ SchedLayout sched_layout(const Dims& d, int max_slots) {
   size_t off = (64 + units + (size_t)s.slots) * sizeof(int32_t);
   s.slot_base = off;
   if (s.slots > 0) off += units * sizeof(int32_t);
-  s.split_rows = off;
+  s.arrived = off;
   off += (size_t)(s.slots / 2) * sizeof(int32_t);
   off = (off + 255) & ~(size_t)255;
   s.parts = off;
@@ -1044,7 +1040,7 @@ hipError_t launch_attn(const Dims& d, float scale, const uint16_t* q, const uint
   a.q = q; a.k = k; a.v = v; a.o = o;
   a.row_ptr = row_ptr; a.col_idx = col_idx; a.col_cap = col_cap;
   a.order = nullptr; a.counter = nullptr; a.one_shot = 0; a.static_list = 0;
-  a.slot_base = nullptr; a.split_rows = nullptr; a.parts = nullptr; a.split_slots = 0; a.grid = 0;
+  a.slot_base = nullptr; a.arrived = nullptr; a.parts = nullptr; a.split_slots = 0; a.grid = 0;
   a.n = d.n; a.nb = d.nb; a.hq = d.hq; a.hkv = d.hkv; a.G = d.G;
   a.c = scale * kLog2e;
   int grid;
@@ -1065,17 +1061,22 @@ hipError_t launch_attn(const Dims& d, float scale, const uint16_t* q, const uint
     a.order = reinterpret_cast<const int32_t*>(sc) + 64;
     const int pg = d.B == 128 ? persistent_grid<128>() : persistent_grid<64>();
     // short layers with at least a persistent grid's worth of units: one unit per workgroup
-    const bool short_one = d.n <= kStaticListMaxLen && (size_t)d.hq * d.nb >= (size_t)pg;
+    // (no row is split there: with every CU slot filled, half rows at 2k tokens and 32 heads
+    // took 56 us where whole ones take 45)
+    const size_t units = (size_t)d.hq * d.nb;
+    const bool short_one = d.n <= kStaticListMaxLen && units >= (size_t)pg;
     a.one_shot = d.n >= kOneShotMinLen || short_one ? 1 : 0;
     a.static_list = d.n <= kStaticListMaxLen ? 1 : 0;
     a.split_slots = short_one ? 0 : sl.slots;  // the slots stay reserved, unused
     if (a.split_slots > 0) {
       a.slot_base = reinterpret_cast<int*>(sc + sl.slot_base);
-      a.split_rows = reinterpret_cast<int*>(sc + sl.split_rows);
+      a.arrived = reinterpret_cast<int*>(sc + sl.arrived);
       a.parts = reinterpret_cast<float*>(sc + sl.parts);
     }
-    grid = a.one_shot || pg > d.hq * d.nb ? d.hq * d.nb : pg;
-    a.grid = grid;
+    // items: the units, and at most one less than the slots more where rows are split
+    const size_t items = units + (a.split_slots > 0 ? (size_t)a.split_slots - 1 : 0);
+    grid = (int)(a.one_shot || items < (size_t)pg ? items : (size_t)pg);
+    a.grid = grid < pg ? grid : pg;
     hipLaunchKernelGGL(attn_schedule, dim3(1), dim3(1024), 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1085,12 +1086,7 @@ hipError_t launch_attn(const Dims& d, float scale, const uint16_t* q, const uint
     e = dense ? launch_t<128, true>(a, grid, stream) : launch_t<128, false>(a, grid, stream);
   else
     e = launch_t<64, false>(a, grid, stream);  // dense 64-row layers run as 128-row ones (above)
-  if (e != hipSuccess || a.split_slots == 0) return e;
-  if (d.B == 128)
-    hipLaunchKernelGGL(attn_combine<128>, dim3(a.split_slots / 2), dim3(kCombineThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(attn_combine<64>, dim3(a.split_slots / 2), dim3(kCombineThreads), 0, stream, a);
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace crisp

@@ -219,6 +219,43 @@ def test_split_rows(case):
         PR.compare_attention(to_f64(o1[h]), to_f64(o_fixed[h]), rows=rows, where=f"{case} h{h} vs fixed")
 
 
+@pytest.mark.parametrize("n,block", [(16384, 128), (8100, 64)])
+def test_split_rows_many_chunks(n, block):
+    """Rows split into 2 to 16 chunks (8 entries each: every other row lists two blocks), odd
+    counts among them, so that the pairwise merge passes chunks without a sibling up the
+    tree: against float64 attention, bitwise repeatable, and within the attention tolerance
+    of the unsplit fixed-order launch."""
+    C = _crisp()
+    _say(f"split rows, many chunks: n={n} B={block}")
+    nb = O.n_blocks(n, block)
+    hq = 2
+    lengths = [9, 16, 17, 25, 33, 40, 41, 56, 64, 65, 72, 89, 104, 113, 120]
+    long_rows = {nb - 1 - i: ln for i, ln in enumerate(lengths) if ln <= nb - i}
+    sets = []
+    for qb in range(nb):
+        ln = long_rows.get(qb)
+        sets.append(sorted({0, qb}) if ln is None else sorted({round(x) for x in np.linspace(0, qb, ln)}))
+    flat = np.concatenate([np.asarray(r, np.int32) for r in sets])
+    rp = np.zeros((hq, nb + 1), np.int32)
+    rp[:, 1:] = np.cumsum([len(r) for r in sets])
+    ci = np.zeros((hq, nb * (nb + 1) // 2), np.int32)
+    ci[:, :len(flat)] = flat
+    q, k, v = _rand(hq, n, seed=31), _rand(1, n, seed=32), _rand(1, n, seed=33)
+    args = (q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(rp).to(DEV), torch.from_numpy(ci).to(DEV), block)
+    runs = [C.crisp_sparse_attn(*args) for _ in range(4)]
+    o_fixed = C.crisp_sparse_attn(*args, balance=False)
+    torch.cuda.synchronize()
+    assert all(torch.equal(runs[0], r) for r in runs[1:])
+    Q, K, V = to_f64(q), to_f64(k)[0], to_f64(v)[0]
+    qbs = sorted(long_rows) + [0, nb // 2]
+    rows = PR.qb_rows(sorted(qbs), block, n)
+    assert not torch.equal(runs[0][:, rows], o_fixed[:, rows]), "no row was split"
+    for h in range(hq):
+        ref = O.sparse_attention(Q[h], K, V, sets, block, 1 / math.sqrt(128), qbs=sorted(qbs))
+        PR.compare_attention(to_f64(runs[0][h]), ref, rows=rows, where=f"many chunks n{n} h{h}")
+        PR.compare_attention(to_f64(runs[0][h]), to_f64(o_fixed[h]), rows=rows, where=f"many chunks n{n} h{h} vs fixed")
+
+
 def test_more_than_2p21_units():
     """A layer with more (head, query block) units than a split work item can name
     (2^21): 65 query heads over one KV head at the longest length with B = 64 (2,129,920
