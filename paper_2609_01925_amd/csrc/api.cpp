@@ -440,9 +440,9 @@ crisp_status crisp_prefill_attn(const crisp_shape* shape, const crisp_params* pa
   const float scale = scale_of(params->softmax_scale);
   hipStream_t st = (hipStream_t)stream;
   const bool by_jsd = params->route_mode == CRISP_ROUTE_BY_JSD;
-  // Short layers: the selection forms p_v and p_s itself from the estimator's sums (one
+  // Short and mid-size layers: the selection forms p_v and p_s itself from the estimator's sums (one
   // launch fewer); the pattern search reads p_v, so it keeps the estimator's own step.
-  const bool fold = !by_jsd && d.nb <= kSmallSelectBlocks;
+  const bool fold = !by_jsd && d.nb <= kFoldBlocks;
   CHECK(hip_status(launch_estimate(d, scale, params->w_sink, params->w_local, q, k, cs, pv, ps, ws, st, fold),
                    "crisp_prefill_attn estimate launch"));
   if (by_jsd)  // the route score slot then holds D_JS instead of C_struct

@@ -112,21 +112,39 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 
 __device__ __forceinline__ int div_up(int a, int b) { return (a + b - 1) / b; }
 
-// Wave-wide sums.
+// Wave-wide reductions: a butterfly over lane distances 32, 16, 8, 4, 2, 1, so every lane gets
+// the same value.  Distances 32 and 16 exchange half-waves and rows (v_permlane32_swap and
+// v_permlane16_swap with both operands = x leave each lane its own value and its partner's);
+// the rest are DPP rotations within a row of 16: once the values repeat every 2 d lanes, the
+// lane d further on holds what the lane at distance d holds.  These are register moves of a
+// few cycles; the LDS-routed shuffles they replace cost about 60 per step.
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_move(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t x, Op op) {
+  const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = op(h[0], h[1]);
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = op(r[0], r[1]);
+  x = op(x, row_move<0x128>(x));  // row_ror:8
+  x = op(x, row_move<0x124>(x));
+  x = op(x, row_move<0x122>(x));
+  return op(x, row_move<0x121>(x));
+}
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-  return x;
+  return __uint_as_float(wave_reduce(__float_as_uint(x), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
 }
 __device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
+  return __uint_as_float(wave_reduce(__float_as_uint(x), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
 }
 __device__ __forceinline__ int wave_sum_i(int x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-  return x;
+  return (int)wave_reduce((uint32_t)x, [](uint32_t a, uint32_t b) { return a + b; });
 }
 
 // The proxy's mass in key block J summed over the b proxy rows (the vertical and slash
@@ -134,26 +152,23 @@ __device__ __forceinline__ int wave_sum_i(int x) {
 // max m they were summed under, -), and lane l takes rows l and l + 64 (ok0 / ok1: the
 // row exists) with their normalisers mcl = M c + log2 L.  *slo and *shi get the sums of
 // lo and hi, each a fixed-order butterfly over the wave, scaled by 2^(m c - mcl).
-__device__ __forceinline__ void proxy_block_sums(const float4* P, int J, float c, float mcl0, float mcl1, bool ok0,
-                                                 bool ok1, float* slo, float* shi) {
-  const int l = __lane_id();
+// proxy_row_sums does the arithmetic on the lane's two pairs e0 and e1.
+__device__ __forceinline__ void proxy_row_sums(float4 e0, float4 e1, float c, float mcl0, float mcl1, bool ok0, bool ok1,
+                                               float* slo, float* shi) {
   float lo0 = 0.f, hi0 = 0.f, lo1 = 0.f, hi1 = 0.f;
   if (ok0) {
-    const float4 e = P[(size_t)J * 128 + l];
-    const float f = e.z == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(e.z * c - mcl0);
-    lo0 = e.x * f;
-    hi0 = e.y * f;
+    const float f = e0.z == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(e0.z * c - mcl0);
+    lo0 = e0.x * f;
+    hi0 = e0.y * f;
   }
   if (ok1) {
-    const float4 e = P[(size_t)J * 128 + l + 64];
-    const float f = e.z == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(e.z * c - mcl1);
-    lo1 = e.x * f;
-    hi1 = e.y * f;
+    const float f = e1.z == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(e1.z * c - mcl1);
+    lo1 = e1.x * f;
+    hi1 = e1.y * f;
   }
   *slo = wave_sum(lo0 + lo1);
   *shi = wave_sum(hi0 + hi1);
 }
-
 #if defined(__HIP_DEVICE_COMPILE__)
 
 // Tile fetch: a 64-key x 128-dim tile goes straight from global memory into an

@@ -57,10 +57,13 @@ hipError_t launch_estimate(const Dims& d, float scale, int w_sink, int w_local, 
 
 // Layers of at most this many blocks take the one-launch-per-head selection.
 constexpr int kSmallSelectBlocks = 64;
+// Up to this many blocks one workgroup per head selects from the pooled logits on, and in
+// prefill forms the head's p_v and p_s from the estimator's sums.
+constexpr int kFoldBlocks = 256;
 
 // route_score is C_struct (tau = tau_proxy) or D_JS (tau = tau_jsd); vs_mode 0 is the
 // noise floor (floor_mode 0: mean, 1: median), 1 gamma coverage; kbar_all: K_bar of
-// every KV group is already in ws.  scores_from_ws (layers of at most kSmallSelectBlocks
+// every KV group is already in ws.  scores_from_ws (layers of at most kFoldBlocks
 // blocks, after launch_estimate with combine_only on the same ws): p_v and p_s are not
 // read; the selection forms them from the estimator's sums in ws.
 hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, float gamma, int k_min, int vs_mode,

@@ -294,25 +294,38 @@ __global__ __launch_bounds__(1024) void est_combine(EstArgs a) {
   combine_head(a, blockIdx.x, red);
 }
 
+constexpr int kScaleRun = 2;
+
 // p_v[J] = (1/b) sum_r (lo + hi)[r][J] 2^(m c - mcl_r);  p_s[J] = (1/b) sum_r (lo[r][J] +
-// hi[r][J - 1]) scaled alike, for the run of blocks [Ja, Jb) of head h, by one wave:
+// hi[r][J - 1]) scaled alike, for the run of blocks [Ja, Jb) (at most kScaleRun) of head h, by one wave:
 // lanes take rows l and l + 64, and a block's row sum is a fixed-order butterfly.
 __device__ __forceinline__ void scale_run(const EstArgs& a, int h, int Ja, int Jb) {
   const int l = threadIdx.x & 63;
   const bool ok0 = l < a.b, ok1 = l + 64 < a.b;
   const float mcl0 = ok0 ? a.rowfinal[(size_t)h * 128 + l] : 0.f;
   const float mcl1 = ok1 ? a.rowfinal[(size_t)h * 128 + l + 64] : 0.f;
+  // the run's blocks and the one before it, all their loads in flight together (one memory
+  // latency per run)
   const float4* P = a.parts + (size_t)h * a.nb * 128;
-  float prev_hi = 0.f;
-  if (Ja > 0) {
-    float slo;
-    proxy_block_sums(P, Ja - 1, a.c, mcl0, mcl1, ok0, ok1, &slo, &prev_hi);
+  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 e0[kScaleRun + 1], e1[kScaleRun + 1];
+#pragma unroll
+  for (int x = 0; x <= kScaleRun; ++x) {
+    const int J = Ja - 1 + x;
+    const bool in = J >= 0 && J < Jb;
+    e0[x] = in && ok0 ? P[(size_t)J * 128 + l] : z;
+    e1[x] = in && ok1 ? P[(size_t)J * 128 + l + 64] : z;
   }
+  float prev_hi = 0.f;
   const float invb = 1.f / (float)a.b;
-  for (int J = Ja; J < Jb; ++J) {
+#pragma unroll
+  for (int x = 0; x <= kScaleRun; ++x) {
+    const int J = Ja - 1 + x;
+    if (J < 0) continue;
+    if (J >= Jb) break;
     float slo, shi;
-    proxy_block_sums(P, J, a.c, mcl0, mcl1, ok0, ok1, &slo, &shi);
-    if (l == 0) {
+    proxy_row_sums(e0[x], e1[x], a.c, mcl0, mcl1, ok0, ok1, &slo, &shi);
+    if (x > 0 && l == 0) {
       a.p_v[(size_t)h * a.nb + J] = (slo + shi) * invb;
       a.p_s[(size_t)h * a.nb + J] = (slo + prev_hi) * invb;
     }
@@ -321,7 +334,6 @@ __device__ __forceinline__ void scale_run(const EstArgs& a, int h, int Ja, int J
 }
 
 // Each wave takes kScaleRun consecutive blocks.  grid (hq, ceil(runs / 4)), 256 threads.
-constexpr int kScaleRun = 2;
 __global__ __launch_bounds__(256) void est_scale(EstArgs a) {
   const int Ja = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kScaleRun;
   if (Ja >= a.nb) return;

@@ -24,7 +24,8 @@
 // CSR: count per row -> per-head scan -> fill, one wave per row, ballots for
 // compaction; rows always hold the sink block 0 and the diagonal block qb.
 // Short layers (N_b <= 64): after the pooling, one workgroup per head takes all of the
-// above with every intermediate in LDS and the VS directions one wave each (sel_small).
+// above with every intermediate in LDS and the VS directions one wave each (sel_small);
+// mid-size ones (N_b <= 256): one workgroup per head after the pooled logits (sel_mid).
 #include "crisp_device.h"
 #include "crisp_internal.h"
 
@@ -72,8 +73,8 @@ struct SelArgs {
 };
 
 constexpr int kRadixBins = 2048;
-constexpr int64_t kSmallCap = 32768;  // causal pairs per head up to which one workgroup finds the PE cutoff
 constexpr double kFix = 1152921504606846976.0;  // 2^60
+constexpr int kMidBlocks = kFoldBlocks;  // up to this many blocks the lists of a head come from one workgroup
 
 __device__ __forceinline__ uint32_t fbits(float x) {
   uint32_t b = __float_as_uint(x);
@@ -321,21 +322,17 @@ struct VsShared {
   int sh[2];
 };
 
-// Route (Alg. 2, or App. A's pattern search when the score is D_JS) and VS selection of
-// direction dir (Alg. 3, or App. A's gamma coverage) of head h.  1024 threads.
-__device__ void route_vs_dir(const SelArgs& a, int h, int dir, VsShared& vsh) {
+// VS selection of one direction (Alg. 3, or App. A's gamma coverage) of a head from its
+// nb scores p, marked in m (and in dm, if given); no block when the head is not VS or nb <= 2.
+// 1024 threads.
+__device__ void vs_dir(const SelArgs& a, bool vs, const float* p, uint8_t* m, uint8_t* dm, VsShared& vsh) {
   uint32_t* hist = vsh.hist;
   unsigned long long* hist64 = vsh.hist64;
   unsigned long long* sh64 = vsh.sh64;
   int* wtot = vsh.wtot;
   int* sh = vsh.sh;
   const int tid = threadIdx.x;
-  const bool vs = a.c_struct[h] >= a.tau;
-  if (dir == 0 && tid == 0) a.route[h] = vs ? 0 : 1;
   const int nb = a.nb;
-  const float* p = (dir == 0 ? a.p_v : a.p_s) + (size_t)h * nb;
-  uint8_t* m = a.masks + ((size_t)h * 2 + dir) * nb;
-  uint8_t* dm = a.dir_mask ? a.dir_mask + ((size_t)h * 2 + dir) * nb : nullptr;
   if (!vs || nb <= 2) {
     for (int J = tid; J < nb; J += 1024) {
       m[J] = 0;
@@ -401,10 +398,15 @@ __device__ void route_vs_dir(const SelArgs& a, int h, int dir, VsShared& vsh) {
   select_top_k(p, nb, kd, m, dm, hist, sh, wtot);
 }
 
-// grid (hq, 2), 1024 threads.
+// Route (Alg. 2, or App. A's pattern search when the score is D_JS) and VS selection of one
+// direction.  grid (hq, 2), 1024 threads.
 __global__ __launch_bounds__(1024) void sel_route_vs(SelArgs a) {
   __shared__ VsShared vsh;
-  route_vs_dir(a, blockIdx.x, blockIdx.y, vsh);
+  const int h = blockIdx.x, dir = blockIdx.y;
+  const bool vs = a.c_struct[h] >= a.tau;
+  if (dir == 0 && threadIdx.x == 0) a.route[h] = vs ? 0 : 1;
+  const size_t at = ((size_t)h * 2 + dir) * a.nb;
+  vs_dir(a, vs, (dir == 0 ? a.p_v : a.p_s) + (size_t)h * a.nb, a.masks + at, a.dir_mask ? a.dir_mask + at : nullptr, vsh);
 }
 
 // Mean of rows [r0, r1) of a [rows][128] bf16 tensor into dst[0..128) (fp32).  256 threads.
@@ -542,7 +544,7 @@ constexpr int kLogitDirect = 512;
 // register i, column = lane % 32.
 __global__ __launch_bounds__(256) void sel_pe_logits_direct(SelArgs a) {
   const int h = blockIdx.y, tid = threadIdx.x;
-  if (a.route[h] != 1) return;
+  if (a.c_struct[h] >= a.tau) return;  // VS head (the route is written by a later launch)
   const int t = blockIdx.x;
   int qt = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
   while ((qt + 1) * (qt + 2) / 2 <= t) ++qt;
@@ -911,14 +913,19 @@ __global__ __launch_bounds__(256) void sel_radix_scan(SelArgs a, int pass) {
   for (int i = tid; i < kRadixBins; i += 256) H[i] = 0ull;
 }
 
-// PE cutoff of a small layer (at most kSmallCap causal pairs per head) in one
-// workgroup per head: the three digit passes of sel_radix_hist / sel_radix_scan
-// with the histograms in LDS.  The masses are the same fixed-point integers, so
-// t*, the remaining mass and the count of pairs equal to t* are the same; one
-// launch replaces seven.  At holds the head's cap scores (global memory or LDS); the
-// state ends in sst (LDS) and, when out is given, in *out.
-__device__ void radix_small_head(const SelArgs& a, const float* At, unsigned long long* bins, RState& sst,
-                                 RState* out) {
+// PE cutoff of a head whose scores fit one workgroup: the three digit passes of
+// sel_radix_hist / sel_radix_scan with the histograms in LDS.  The masses are the same
+// fixed-point integers, so t*, the remaining mass and the count of pairs equal to t* are
+// the same.  At holds the head's cap scores (LDS, all at most 1), bins kRadixBins masses;
+// the state ends in sst.  The first digit sees every score and the scores of a head share a
+// few exponents, so its LDS atomics meet on few addresses, one after the other: a score of
+// at most 1 has a first digit below 512, which leaves room for four copies of each bin (one
+// per lane mod 4), folded before the search.  They pay from a few thousand scores on
+// (sel_mid at 157 blocks 40.4 -> 33.0 us, at 79 blocks 20.6 -> 18.8); at the 2080 scores
+// of 64 blocks the folding costs more (sel_small 16.4 -> 17.6).  Four digits of 8 bits or
+// fewer with 8 or 16 copies each: sel_small 19.0-21.5 us.
+template <int kCopies>
+__device__ void radix_head(const SelArgs& a, const float* At, unsigned long long* bins, RState& sst) {
   const int tid = threadIdx.x, nthr = blockDim.x;
   if (tid == 0) {
     sst.prefix = 0;
@@ -928,19 +935,38 @@ __device__ void radix_small_head(const SelArgs& a, const float* At, unsigned lon
     sst.ceq = 0;
     sst.pad = 0;
   }
+  constexpr int kTopBins = 512;
+  static_assert(kTopBins * kCopies <= kRadixBins, "bins");
   for (int pass = 0; pass < 3; ++pass) {
     int shift, nbits;
     radix_digit(pass, shift, nbits);
-    const int nbins = 1 << nbits;
-    for (int i = tid; i < nbins; i += nthr) bins[i] = 0ull;
+    const int nbins = pass == 0 ? kTopBins : 1 << nbits;
+    for (int i = tid; i < kRadixBins; i += nthr) bins[i] = 0ull;
     __syncthreads();  // bins cleared; sst of the previous pass visible
     if (sst.all) break;
-    const int hi = shift + nbits;
-    const uint64_t want = (uint64_t)sst.prefix >> hi;
-    const uint32_t dmask = (uint32_t)nbins - 1u;
-    for (int64_t i = tid; i < a.cap; i += nthr) {
-      const uint32_t b = fbits(At[i]);
-      if (((uint64_t)b >> hi) == want) atomicAdd(&bins[(b >> shift) & dmask], fixed_mass(b));
+    if (pass == 0) {
+#pragma unroll 2
+      for (int i = tid; i < (int)a.cap; i += nthr) {
+        const uint32_t b = fbits(At[i]), d = b >> shift;
+        atomicAdd(&bins[(d < kTopBins ? d : kTopBins - 1) * kCopies + (tid & (kCopies - 1))], fixed_mass(b));
+      }
+      if (kCopies > 1) {
+        __syncthreads();
+        unsigned long long sum = 0ull;
+        if (tid < kTopBins)
+#pragma unroll
+          for (int x = 0; x < kCopies; ++x) sum += bins[tid * kCopies + ((x + tid) & (kCopies - 1))];
+        __syncthreads();
+        if (tid < kTopBins) bins[tid] = sum;
+      }
+    } else {
+      const int hi = shift + nbits;
+      const uint32_t want = sst.prefix >> hi, dmask = (uint32_t)nbins - 1u;
+#pragma unroll 2
+      for (int i = tid; i < (int)a.cap; i += nthr) {
+        const uint32_t b = fbits(At[i]);
+        if (b >> hi == want) atomicAdd(&bins[(b >> shift) & dmask], fixed_mass(b));
+      }
     }
     __syncthreads();
     if (tid < 64) {
@@ -962,28 +988,15 @@ __device__ void radix_small_head(const SelArgs& a, const float* At, unsigned lon
     }
     __syncthreads();  // the search is done with the bins before the next pass clears them
   }
-  if (tid == 0 && out) *out = sst;
 }
 
-// grid hq, 1024 threads.
-__global__ __launch_bounds__(1024) void sel_radix_small(SelArgs a) {
-  __shared__ unsigned long long bins[kRadixBins];
-  __shared__ RState sst;
-  const int h = blockIdx.x;
-  if (a.route[h] != 1) return;
-  radix_small_head(a, a.atil + (size_t)h * a.cap, bins, sst, a.rstate + h);
-}
-
-// Per-row counts.  VS: x = row size.  PE: x = #(> t*), y = #(== t*), z = flags
-// (1: block 0 > t*, 2: block 0 == t*, 4: block qb > t*, 8: block qb == t*).
-// grid (ceil(nb / 4), hq), 256 threads, one wave per row.
-__device__ __forceinline__ void csr_count_row(const SelArgs& a, int h, int qb) {
+// Per-row counts of row qb, by one wave.  VS (vm, sm: the head's direction masks): x = row
+// size.  PE (row: its scores): x = #(> t*), y = #(== t*), z = flags (1: block 0 > t*, 2:
+// block 0 == t*, 4: block qb > t*, 8: block qb == t*).
+__device__ __forceinline__ int4 csr_count_row(bool vs, int nb, int qb, const uint8_t* vm, const uint8_t* sm,
+                                              const RState& st, const float* row) {
   const int l = threadIdx.x & 63;
-  const int nb = a.nb;
-  int4 info = make_int4(0, 0, 0, 0);
-  if (a.route[h] == 0) {
-    const uint8_t* vm = a.masks + (size_t)h * 2 * nb;
-    const uint8_t* sm = vm + nb;
+  if (vs) {
     int cnt = 0;
     for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
       bool sel[4];
@@ -995,54 +1008,49 @@ __device__ __forceinline__ void csr_count_row(const SelArgs& a, int h, int qb) {
 #pragma unroll
       for (int x = 0; x < 4; ++x) cnt += __popcll(__ballot(sel[x]));
     }
-    info.x = cnt;
-  } else {
-    const RState st = a.rstate[h];
-    const float* row = a.atil + (size_t)h * a.cap + (int64_t)qb * (qb + 1) / 2;
-    int ngt = 0, neq = 0, flags = 0;
-    for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
-      uint32_t bv[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const int kb = base + 64 * x + l;
-        bv[x] = kb <= qb ? fbits(row[kb]) : 0u;
-      }
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        if (base + 64 * x > qb) break;
-        const int kb = base + 64 * x + l;
-        const uint32_t b = bv[x];
-        const bool gt = kb <= qb && (st.all || b > st.prefix);
-        const bool eq = kb <= qb && !st.all && b == st.prefix;
-        ngt += __popcll(__ballot(gt));
-        neq += __popcll(__ballot(eq));
-        if (base + 64 * x == 0 || qb - (base + 64 * x) < 64) {  // the chunk holds block 0 or block qb
-          int f = 0;
-          if (kb == 0) f |= (gt ? 1 : 0) | (eq ? 2 : 0);
-          if (kb == qb) f |= (gt ? 4 : 0) | (eq ? 8 : 0);
-          f = wave_sum_i(f);  // at most two lanes contribute, with disjoint bits
-          flags |= f;
-        }
-      }
-    }
-    info = make_int4(ngt, neq, flags, 0);
+    return make_int4(cnt, 0, 0, 0);
   }
-  if (l == 0) a.rowinfo[(size_t)h * nb + qb] = info;
+  int ngt = 0, neq = 0, flags = 0;
+  for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
+    uint32_t bv[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int kb = base + 64 * x + l;
+      bv[x] = kb <= qb ? fbits(row[kb]) : 0u;
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      if (base + 64 * x > qb) break;
+      const int kb = base + 64 * x + l;
+      const uint32_t b = bv[x];
+      const bool gt = kb <= qb && (st.all || b > st.prefix);
+      const bool eq = kb <= qb && !st.all && b == st.prefix;
+      const uint64_t gm = __ballot(gt), em = __ballot(eq);
+      ngt += __popcll(gm);
+      neq += __popcll(em);
+      if (base + 64 * x == 0) flags |= (int)(gm & 1) | (int)((em & 1) << 1);
+      if (qb - (base + 64 * x) < 64)
+        flags |= (int)(((gm >> (qb & 63)) & 1) << 2) | (int)(((em >> (qb & 63)) & 1) << 3);
+    }
+  }
+  return make_int4(ngt, neq, flags, 0);
 }
 
+// grid (ceil(nb / 4), hq), 256 threads, one wave per row.
 __global__ __launch_bounds__(256) void sel_csr_count(SelArgs a) {
-  const int qb = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (qb < a.nb) csr_count_row(a, blockIdx.y, qb);
+  const int qb = blockIdx.x * 4 + (threadIdx.x >> 6), h = blockIdx.y, nb = a.nb;
+  if (qb >= nb) return;
+  const bool vs = a.route[h] == 0;
+  const uint8_t* vm = a.masks + (size_t)h * 2 * nb;
+  const RState st = vs ? RState{} : a.rstate[h];
+  const int4 info = csr_count_row(vs, nb, qb, vm, vm + nb, st, a.atil + (size_t)h * a.cap + (int64_t)qb * (qb + 1) / 2);
+  if ((threadIdx.x & 63) == 0) a.rowinfo[(size_t)h * nb + qb] = info;
 }
 
-// Ties taken per PE row, row sizes and the exclusive scan into row_ptr.  grid hq, 1024 threads.
-__device__ __forceinline__ void csr_scan_head(const SelArgs& a, int h, long long* wtot) {
+// Ties taken per PE row (into info[qb].w), row sizes and their exclusive scan into rp[0 ..
+// nb].  1024 threads.
+__device__ __forceinline__ void csr_scan_head(bool pe, int nb, const RState& st, int4* info, int32_t* rp, long long* wtot) {
   const int tid = threadIdx.x, w = tid >> 6;
-  const int nb = a.nb;
-  const bool pe = a.route[h] == 1;
-  const RState st = pe ? a.rstate[h] : RState{};
-  int4* info = a.rowinfo + (size_t)h * nb;
-  int32_t* rp = a.row_ptr + (size_t)h * (nb + 1);
   long long tie_carry = 0, row_carry = 0;
   for (int base = 0; base < nb; base += 1024) {
     const int qb = base + tid;
@@ -1050,11 +1058,7 @@ __device__ __forceinline__ void csr_scan_head(const SelArgs& a, int h, long long
     // inclusive scans (ties, then row sizes) by waves + wave totals
     long long cnt = 0;
     if (pe) {
-      long long x = in.y, incl = x;
-      for (int o = 1; o < 64; o <<= 1) {
-        const long long y = __shfl_up(incl, o);
-        if ((tid & 63) >= o) incl += y;
-      }
+      const long long x = in.y, incl = (long long)wave_inclusive_scan((unsigned long long)x);
       if ((tid & 63) == 63) wtot[w] = incl;
       __syncthreads();
       long long before = 0, all = 0;
@@ -1081,11 +1085,7 @@ __device__ __forceinline__ void csr_scan_head(const SelArgs& a, int h, long long
     } else if (qb < nb) {
       cnt = in.x;
     }
-    long long incl = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-      const long long y = __shfl_up(incl, o);
-      if ((tid & 63) >= o) incl += y;
-    }
+    const long long incl = (long long)wave_inclusive_scan((unsigned long long)cnt);
     if ((tid & 63) == 63) wtot[w] = incl;
     __syncthreads();
     long long before = 0, all = 0;
@@ -1100,21 +1100,21 @@ __device__ __forceinline__ void csr_scan_head(const SelArgs& a, int h, long long
   if (tid == 0) rp[nb] = (int32_t)row_carry;
 }
 
+// grid hq, 1024 threads.
 __global__ __launch_bounds__(1024) void sel_csr_scan(SelArgs a) {
   __shared__ long long wtot[16];
-  csr_scan_head(a, blockIdx.x, wtot);
+  const int h = blockIdx.x;
+  const bool pe = a.route[h] == 1;
+  csr_scan_head(pe, a.nb, pe ? a.rstate[h] : RState{}, a.rowinfo + (size_t)h * a.nb, a.row_ptr + (size_t)h * (a.nb + 1), wtot);
 }
 
-// Write the block lists.  grid (ceil(nb / 4), hq), 256 threads, one wave per row.
-__device__ __forceinline__ void csr_fill_row(const SelArgs& a, int h, int qb) {
+// Writes the list of row qb at out, by one wave; take: the ties of a PE row to take.
+__device__ __forceinline__ void csr_fill_row(bool vs, int nb, int qb, const uint8_t* vm, const uint8_t* sm,
+                                             const RState& st, const float* row, int take, int32_t* out) {
   const int l = threadIdx.x & 63;
-  const int nb = a.nb;
-  int32_t* out = a.col_idx + (size_t)h * a.col_cap + a.row_ptr[(size_t)h * (nb + 1) + qb];
   const uint64_t lt = lanemask_lt();
   int pos = 0;
-  if (a.route[h] == 0) {
-    const uint8_t* vm = a.masks + (size_t)h * 2 * nb;
-    const uint8_t* sm = vm + nb;
+  if (vs) {
     for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
       bool sv[4];
 #pragma unroll
@@ -1130,40 +1130,276 @@ __device__ __forceinline__ void csr_fill_row(const SelArgs& a, int h, int qb) {
         pos += __popcll(bal);
       }
     }
-  } else {
-    const RState st = a.rstate[h];
-    const int take = a.rowinfo[(size_t)h * nb + qb].w;
-    const float* row = a.atil + (size_t)h * a.cap + (int64_t)qb * (qb + 1) / 2;
-    int eq_seen = 0;
-    for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
-      uint32_t bv[4];
+    return;
+  }
+  int eq_seen = 0;
+  for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
+    uint32_t bv[4];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const int kb = base + 64 * x + l;
-        bv[x] = kb <= qb ? fbits(row[kb]) : 0u;
-      }
+    for (int x = 0; x < 4; ++x) {
+      const int kb = base + 64 * x + l;
+      bv[x] = kb <= qb ? fbits(row[kb]) : 0u;
+    }
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        if (base + 64 * x > qb) break;
-        const int kb = base + 64 * x + l;
-        const uint32_t b = bv[x];
-        const bool gt = kb <= qb && (st.all || b > st.prefix);
-        const bool eq = kb <= qb && !st.all && b == st.prefix;
-        const uint64_t eb = __ballot(eq);
-        const int eq_rank = eq_seen + __popcll(eb & lt);
-        eq_seen += __popcll(eb);
-        const bool sel = kb <= qb && (gt || (eq && eq_rank < take) || kb == 0 || kb == qb);
-        const uint64_t bal = __ballot(sel);
-        if (sel) out[pos + __popcll(bal & lt)] = kb;
-        pos += __popcll(bal);
-      }
+    for (int x = 0; x < 4; ++x) {
+      if (base + 64 * x > qb) break;
+      const int kb = base + 64 * x + l;
+      const uint32_t b = bv[x];
+      const bool gt = kb <= qb && (st.all || b > st.prefix);
+      const bool eq = kb <= qb && !st.all && b == st.prefix;
+      const uint64_t eb = __ballot(eq);
+      const int eq_rank = eq_seen + __popcll(eb & lt);
+      eq_seen += __popcll(eb);
+      const bool sel = kb <= qb && (gt || (eq && eq_rank < take) || kb == 0 || kb == qb);
+      const uint64_t bal = __ballot(sel);
+      if (sel) out[pos + __popcll(bal & lt)] = kb;
+      pos += __popcll(bal);
     }
   }
 }
 
+// grid (ceil(nb / 4), hq), 256 threads, one wave per row.
 __global__ __launch_bounds__(256) void sel_csr_fill(SelArgs a) {
-  const int qb = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (qb < a.nb) csr_fill_row(a, blockIdx.y, qb);
+  const int qb = blockIdx.x * 4 + (threadIdx.x >> 6), h = blockIdx.y, nb = a.nb;
+  if (qb >= nb) return;
+  const bool vs = a.route[h] == 0;
+  const uint8_t* vm = a.masks + (size_t)h * 2 * nb;
+  csr_fill_row(vs, nb, qb, vm, vm + nb, vs ? RState{} : a.rstate[h], a.atil + (size_t)h * a.cap + (int64_t)qb * (qb + 1) / 2,
+               a.rowinfo[(size_t)h * nb + qb].w, a.col_idx + (size_t)h * a.col_cap + a.row_ptr[(size_t)h * (nb + 1) + qb]);
+}
+
+// p_v and p_s of one head from the estimator's per-(block, row) sums, as its scale step forms
+// them: p_v[J] = (lo[J] + hi[J]) / b, p_s[J] = (lo[J] + hi[J - 1]) / b, every sum in the same
+// order.  1024 threads; bsum and pvs hold 2 x NB floats each.
+template <int NB>
+__device__ __forceinline__ void scores_from_parts(const SelArgs& a, int h, float (*bsum)[NB], float (*pvs)[NB]) {
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, nb = a.nb;
+  const bool ok0 = l < a.b, ok1 = l + 64 < a.b;
+  const float mcl0 = ok0 ? a.rowfinal[(size_t)h * 128 + l] : 0.f;
+  const float mcl1 = ok1 ? a.rowfinal[(size_t)h * 128 + l + 64] : 0.f;
+  const float4* P = a.parts + (size_t)h * nb * 128;
+  for (int J0 = w; J0 < nb; J0 += 64) {  // four blocks of this wave, their loads in flight together
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 e0[4], e1[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int J = J0 + 16 * x;
+      e0[x] = ok0 && J < nb ? P[(size_t)J * 128 + l] : z;
+      e1[x] = ok1 && J < nb ? P[(size_t)J * 128 + l + 64] : z;
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int J = J0 + 16 * x;
+      if (J >= nb) break;
+      float slo, shi;
+      proxy_row_sums(e0[x], e1[x], a.c2, mcl0, mcl1, ok0, ok1, &slo, &shi);
+      if (l == 0) {
+        bsum[0][J] = slo;
+        bsum[1][J] = shi;
+      }
+    }
+  }
+  __syncthreads();
+  const float invb = 1.f / (float)a.b;
+  if (tid < nb) {
+    pvs[0][tid] = (bsum[0][tid] + bsum[1][tid]) * invb;
+    pvs[1][tid] = (bsum[0][tid] + (tid > 0 ? bsum[1][tid - 1] : 0.f)) * invb;
+  }
+  __syncthreads();
+}
+
+// VS selection of one direction (vs_dir) of a VS head of at most 256 blocks, by one wave with
+// blocks l, l + 64, l + 128, l + 192 on lane l: the k-th largest score is the largest t with
+// #{b >= t} >= k and the gamma cut the largest t whose mass at or above it reaches gamma, both
+// found bit by bit from the top with ballots and wave sums (no LDS, no barrier, so the two
+// directions run on two waves at once).
+struct WaveBlocks {
+  uint32_t b[4];  // fbits of the scores, 0 past the last block
+  int lo, hi;     // blocks taken into account: [lo, hi)
+  __device__ __forceinline__ bool in(int e) const {
+    const int J = lane_id() + 64 * e;
+    return J >= lo && J < hi;
+  }
+  __device__ __forceinline__ int count_ge(uint32_t t) const {
+    int n = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n += __popcll(__ballot(in(e) && b[e] >= t));
+    return n;
+  }
+  __device__ uint32_t kth_largest(int k) const {
+    uint32_t t = 0;
+    for (int bit = 31; bit >= 0; --bit)
+      if (count_ge(t | (1u << bit)) >= k) t |= 1u << bit;
+    return t;
+  }
+  // sel[e]: the block is above t or one of the first `ties` equal to t
+  __device__ void take(uint32_t t, int ties, bool (&sel)[4]) const {
+    int seen = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint64_t eq = __ballot(in(e) && b[e] == t);
+      sel[e] = in(e) && (b[e] > t || (b[e] == t && seen + __popcll(eq & lanemask_lt()) < ties));
+      seen += __popcll(eq);
+    }
+  }
+  __device__ void top_k(int k, bool (&sel)[4]) const {
+    const uint32_t t = kth_largest(k);
+    take(t, t == ~0u ? k : k - count_ge(t + 1), sel);
+  }
+};
+
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x) {
+  return lane_value(wave_inclusive_scan(x), 63);
+}
+
+__device__ void mid_vs_dir(const SelArgs& a, const float* P, uint8_t* m, uint8_t* dm) {
+  const int l = lane_id(), nb = a.nb;
+  WaveBlocks w;
+  float p[4];
+  w.lo = 0;
+  w.hi = nb;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    p[e] = w.in(e) ? P[l + 64 * e] : 0.f;
+    w.b[e] = w.in(e) ? fbits(p[e]) : 0u;
+  }
+  bool sel[4];
+  int c = 0;
+  if (a.vs_mode == 1) {
+    const unsigned long long need = (unsigned long long)ceil((double)a.gamma * kFix);
+    unsigned long long mass[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mass[e] = w.in(e) ? fixed_mass(w.b[e]) : 0ull;
+    auto mass_ge = [&](uint32_t t) {
+      unsigned long long x = 0ull;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x += w.b[e] >= t ? mass[e] : 0ull;
+      return wave_sum_u64(x);
+    };
+    if (mass_ge(0u) < need) {  // the total mass never reaches gamma
+      c = nb;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sel[e] = w.in(e);
+    } else {
+      uint32_t t = 0;
+      for (int bit = 31; bit >= 0; --bit)
+        if (mass_ge(t | (1u << bit)) >= need) t |= 1u << bit;
+      const unsigned long long mt = fixed_mass(t);  // > 0: t carries mass
+      const unsigned long long rest = need - mass_ge(t + 1);
+      const int ceq = (int)((rest + mt - 1) / mt);
+      c = w.count_ge(t + 1) + ceq;
+      w.take(t, ceq, sel);
+    }
+  } else {
+    float mu;
+    if (a.floor_mode == 1) {  // median of p[1 .. nb-2]
+      WaveBlocks mid = w;
+      mid.lo = 1;
+      mid.hi = nb - 1;
+      const int n = nb - 2;
+      const float hi = __uint_as_float(mid.kth_largest(n / 2 + (n & 1)));
+      mu = n & 1 ? hi : (__uint_as_float(mid.kth_largest(n / 2 + 1)) + hi) * 0.5f;
+    } else {
+      const float r = fmaxf((1.0f - P[0]) - P[nb - 1], 0.0f);
+      mu = r / (float)(nb - 2);
+    }
+    const float thr = a.alpha * mu;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sel[e] = w.in(e) && p[e] > thr;
+      c += __popcll(__ballot(sel[e]));
+    }
+  }
+  int kd = c > a.k_min ? c : a.k_min;
+  kd = kd < nb ? kd : nb;
+  if (kd != c) w.top_k(kd, sel);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (w.in(e)) {
+      m[l + 64 * e] = sel[e];
+      if (dm) dm[l + 64 * e] = sel[e];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Mid-size layers (kPeSmall < N_b <= kMidBlocks): after the pooling and the pooled logits,
+// the route, the selection and the lists of one head in one workgroup.  A head's causal
+// triangle fits LDS (at most 131 KB), so the row softmax, the radix passes, the counts and
+// the lists work on it there, and seven launches (each about 4.7 us however little it does)
+// become one: at 79 blocks (5k tokens, 64-row blocks) 40 us of launches -> 18.8 us, at 157
+// blocks (20k tokens) 47 -> 33.0.  It is bound by latency: rows and blocks are read four at a
+// time per wave.  The arithmetic and its order are those of sel_pe_softmax and of the separate
+// launches, so the lists are the same.  grid hq, 1024 threads, one workgroup per CU.
+struct MidShared {
+  float at[kMidBlocks * (kMidBlocks + 1) / 2];  // the head's pooled scores, row qb at qb (qb + 1) / 2
+  unsigned long long bins[kRadixBins];
+  int4 info[kMidBlocks];
+  int32_t rp[kMidBlocks + 1];
+  uint8_t masks[2][kMidBlocks];
+  float bsum[2][kMidBlocks], pvs[2][kMidBlocks];
+  long long wtot[16];
+  RState st;
+};
+
+__global__ __launch_bounds__(1024) void sel_mid(SelArgs a) {
+  __shared__ __attribute__((aligned(16))) MidShared sm;
+  const int h = blockIdx.x, tid = threadIdx.x, w = tid >> 6, l = tid & 63, nb = a.nb;
+  const bool vs = a.c_struct[h] >= a.tau;
+  if (tid == 0) a.route[h] = vs ? 0 : 1;
+  if (vs) {
+    const float* p[2] = {a.p_v + (size_t)h * nb, a.p_s + (size_t)h * nb};
+    if (a.parts) {
+      scores_from_parts<kMidBlocks>(a, h, sm.bsum, sm.pvs);
+      p[0] = sm.pvs[0];
+      p[1] = sm.pvs[1];
+    }
+    if (w < 2) mid_vs_dir(a, w == 0 ? p[0] : p[1], sm.masks[w], a.dir_mask ? a.dir_mask + ((size_t)h * 2 + w) * nb : nullptr);
+  } else {
+    if (a.dir_mask)
+      for (int i = tid; i < 2 * nb; i += 1024) a.dir_mask[(size_t)h * 2 * nb + i] = 0;
+    // row softmax over N_b (sel_pe_softmax's reduction order: i with i + 128, with i + 64, then
+    // a butterfly's halving steps), a wave per row, logits straight from global memory
+    const float inv_nb = 1.f / (float)nb;
+    const float* logits = a.atil + (size_t)h * a.cap;
+    for (int q0 = w; q0 < nb; q0 += 64) {  // four rows of this wave, their loads in flight together
+      float x[4][4];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int qb = q0 + 16 * y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          x[y][e] = qb < nb && l + 64 * e <= qb ? logits[qb * (qb + 1) / 2 + l + 64 * e] : -__builtin_inff();
+      }
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int qb = q0 + 16 * y;
+        if (qb >= nb) break;
+        const float mx = wave_max(fmaxf(fmaxf(x[y][0], x[y][2]), fmaxf(x[y][1], x[y][3])));
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = l + 64 * e <= qb ? fast_exp2(x[y][e] - mx) : 0.f;
+        const float sum = wave_sum((p[0] + p[2]) + (p[1] + p[3]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (l + 64 * e <= qb) sm.at[qb * (qb + 1) / 2 + l + 64 * e] = p[e] / sum * inv_nb;
+      }
+    }
+    __syncthreads();
+    radix_head<4>(a, sm.at, sm.bins, sm.st);
+  }
+  __syncthreads();  // the direction masks, or the PE state
+  const RState st = vs ? RState{} : sm.st;
+  for (int qb = w; qb < nb; qb += 16) {
+    const int4 info = csr_count_row(vs, nb, qb, sm.masks[0], sm.masks[1], st, sm.at + qb * (qb + 1) / 2);
+    if (l == 0) sm.info[qb] = info;
+  }
+  __syncthreads();
+  csr_scan_head(!vs, nb, st, sm.info, sm.rp, sm.wtot);
+  __syncthreads();
+  if (tid <= nb) a.row_ptr[(size_t)h * (nb + 1) + tid] = sm.rp[tid];
+  int32_t* out = a.col_idx + (size_t)h * a.col_cap;
+  for (int qb = w; qb < nb; qb += 16)
+    csr_fill_row(vs, nb, qb, sm.masks[0], sm.masks[1], st, sm.at + qb * (qb + 1) / 2, sm.info[qb].w, out + sm.rp[qb]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1172,13 +1408,13 @@ __global__ __launch_bounds__(256) void sel_csr_fill(SelArgs a) {
 // masks as 64-bit words, the pooled scores, the radix bins, the per-row counts and
 // offsets), so no phase waits on a round trip through global memory.  With at most 64
 // blocks a VS direction fits one wave, one block per lane, and both directions run at
-// once on waves 0 and 1.  Their decisions are those of route_vs_dir, reached with
+// once on waves 0 and 1.  Their decisions are those of vs_dir, reached with
 // ballots and lane reads instead of histogram passes: the k-th largest bit pattern is
 // found bit by bit from the top as the largest t with #{b >= t} >= k, and the gamma cut
 // as the largest block value t whose mass at or above t (the same 2^-60 fixed-point
 // integers) reaches gamma -- the values the digit passes settle on, since both counts
 // only fall as t grows.  The PE scores, softmax and cutoff are pe_small_head and
-// radix_small_head on LDS, and the lists follow the rules of csr_count_row,
+// radix_head on LDS, and the lists follow the rules of csr_count_row,
 // csr_scan_head and csr_fill_row, one wave per row.  grid hq, kSmallThreads threads.
 constexpr int kSmallThreads = 1024;
 
@@ -1202,7 +1438,7 @@ __device__ __forceinline__ bool wave_top_k(uint32_t b, bool in, int kd) {
   return in && (b > t || (eq && rank < kd - ngt));
 }
 
-// The block set of one direction of a VS head with nb > 2 blocks (route_vs_dir), lane =
+// The block set of one direction of a VS head with nb > 2 blocks (vs_dir), lane =
 // block; P: the direction's scores (p_v or p_s) of the head.
 __device__ bool small_vs_dir(const SelArgs& a, const float* P) {
   const int l = lane_id(), nb = a.nb;
@@ -1292,27 +1528,7 @@ __global__ __launch_bounds__(kSmallThreads) void sel_small(SelArgs a) {
   if (tid == 0) a.route[h] = vs ? 0 : 1;
   const float* pdir[2] = {a.p_v + (size_t)h * nb, a.p_s + (size_t)h * nb};
   if (vs && a.parts) {
-    // p_v and p_s from the estimator's sums, as its scale step forms them: p_v[J] = (lo[J] +
-    // hi[J]) / b, p_s[J] = (lo[J] + hi[J - 1]) / b, every sum in the same order
-    const bool ok0 = l < a.b, ok1 = l + 64 < a.b;
-    const float mcl0 = ok0 ? a.rowfinal[(size_t)h * 128 + l] : 0.f;
-    const float mcl1 = ok1 ? a.rowfinal[(size_t)h * 128 + l + 64] : 0.f;
-    const float4* P = a.parts + (size_t)h * nb * 128;
-    for (int J = w; J < nb; J += kSmallThreads / 64) {
-      float slo, shi;
-      proxy_block_sums(P, J, a.c2, mcl0, mcl1, ok0, ok1, &slo, &shi);
-      if (l == 0) {
-        sm.bsum[0][J] = slo;
-        sm.bsum[1][J] = shi;
-      }
-    }
-    __syncthreads();
-    const float invb = 1.f / (float)a.b;
-    if (tid < nb) {
-      sm.pvs[0][tid] = (sm.bsum[0][tid] + sm.bsum[1][tid]) * invb;
-      sm.pvs[1][tid] = (sm.bsum[0][tid] + (tid > 0 ? sm.bsum[1][tid - 1] : 0.f)) * invb;
-    }
-    __syncthreads();
+    scores_from_parts<kPeSmall>(a, h, sm.bsum, sm.pvs);
     pdir[0] = sm.pvs[0];
     pdir[1] = sm.pvs[1];
   }
@@ -1325,7 +1541,7 @@ __global__ __launch_bounds__(kSmallThreads) void sel_small(SelArgs a) {
   if (!vs) {
     pe_small_head(a, h, sm.ops, sm.at);
     __syncthreads();  // every score is in sm.at; sm.ops is free
-    radix_small_head(a, sm.at, reinterpret_cast<unsigned long long*>(sm.ops), sm.st, nullptr);
+    radix_head<1>(a, sm.at, reinterpret_cast<unsigned long long*>(sm.ops), sm.st);
   }
   __syncthreads();  // the direction masks, or the PE state
   const uint64_t lt = lanemask_lt();
@@ -1370,12 +1586,7 @@ __global__ __launch_bounds__(kSmallThreads) void sel_small(SelArgs a) {
     int4 in = l < nb ? sm.info[l] : make_int4(0, 0, 0, 0);
     int cnt = in.x;
     if (!vs) {
-      int incl = in.y;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o, 64);
-        if (l >= o) incl += y;
-      }
+      const int incl = (int)wave_inclusive_scan((uint32_t)in.y);
       const unsigned long long tie_prefix = (unsigned long long)(incl - in.y);
       const unsigned long long ceq = sm.st.ceq;
       int take = 0;
@@ -1390,12 +1601,7 @@ __global__ __launch_bounds__(kSmallThreads) void sel_small(SelArgs a) {
       if (l < nb) sm.info[l] = in;
     }
     if (l >= nb) cnt = 0;
-    int incl = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(incl, o, 64);
-      if (l >= o) incl += y;
-    }
+    const int incl = (int)wave_inclusive_scan((uint32_t)cnt);
     int32_t* rp = a.row_ptr + (size_t)h * (nb + 1);
     if (l < nb) {
       sm.rp[l] = incl - cnt;
@@ -1486,7 +1692,7 @@ hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, flo
   a.rstate = reinterpret_cast<RState*>(ws + L.rstate);
   a.rowinfo = reinterpret_cast<int4*>(ws + L.rowinfo);
   const int nb = d.nb;
-  const bool from_ws = scores_from_ws && nb <= kPeSmall;
+  const bool from_ws = scores_from_ws && nb <= kFoldBlocks;
   a.parts = from_ws ? reinterpret_cast<const float4*>(ws + L.parts) : nullptr;
   a.rowfinal = from_ws ? reinterpret_cast<const float*>(ws + L.rowfinal) : nullptr;
   a.b = d.b;
@@ -1495,7 +1701,8 @@ hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, flo
     hipLaunchKernelGGL(sel_small, dim3(d.hq), dim3(kSmallThreads), 0, stream, a);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(sel_route_vs, dim3(d.hq, 2), dim3(1024), 0, stream, a);
+  const bool mid = nb <= kMidBlocks;
+  if (!mid) hipLaunchKernelGGL(sel_route_vs, dim3(d.hq, 2), dim3(1024), 0, stream, a);
   hipLaunchKernelGGL(sel_pool, dim3(nb, d.hq + d.hkv), dim3(256), 0, stream, a);
   if (nb <= kLogitDirect) {
     const int nt = (nb + 63) / 64;
@@ -1504,18 +1711,17 @@ hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, flo
     const int nt = (nb + 127) / 128;
     hipLaunchKernelGGL(sel_pe_logits<64>, dim3(nt * (nt + 1) / 2, d.hq), dim3(256), 0, stream, a);
   }
+  if (mid) {  // a head's scores fit LDS: everything after the logits in one launch
+    hipLaunchKernelGGL(sel_mid, dim3(d.hq), dim3(1024), 0, stream, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(sel_pe_softmax, dim3(nb, d.hq), dim3(256), 0, stream, a);
-  if (d.cap <= kSmallCap) {
-    hipLaunchKernelGGL(sel_radix_small, dim3(d.hq), dim3(1024), 0, stream, a);
-  } else {
-    hipLaunchKernelGGL(sel_radix_init, dim3(d.hq), dim3(256), 0, stream, a);
-    int64_t chunks = (d.cap + 16383) / 16384;
-    if (chunks > 1024) chunks = 1024;
-    if (chunks < 1) chunks = 1;
-    for (int pass = 0; pass < 3; ++pass) {
-      hipLaunchKernelGGL(sel_radix_hist, dim3((unsigned)chunks, d.hq), dim3(256), 0, stream, a, pass);
-      hipLaunchKernelGGL(sel_radix_scan, dim3(d.hq), dim3(256), 0, stream, a, pass);
-    }
+  hipLaunchKernelGGL(sel_radix_init, dim3(d.hq), dim3(256), 0, stream, a);
+  int64_t chunks = (d.cap + 16383) / 16384;
+  if (chunks > 1024) chunks = 1024;
+  for (int pass = 0; pass < 3; ++pass) {
+    hipLaunchKernelGGL(sel_radix_hist, dim3((unsigned)chunks, d.hq), dim3(256), 0, stream, a, pass);
+    hipLaunchKernelGGL(sel_radix_scan, dim3(d.hq), dim3(256), 0, stream, a, pass);
   }
   const int rows_grid = (nb + 3) / 4;
   hipLaunchKernelGGL(sel_csr_count, dim3(rows_grid, d.hq), dim3(256), 0, stream, a);

@@ -806,6 +806,29 @@ def test_median_floor_stress_config4():
                  where="med stress")
 
 
+@pytest.mark.parametrize("n,block", [(8193, 128), (16400, 64), (32768, 128), (32769, 128)])
+@pytest.mark.parametrize("mode", ["floor", "median", "flex"])
+def test_mid_size_selection(n, block, mode):
+    """65, 257, 256 and 257 key blocks: both edges of the sizes whose selection runs in one
+    workgroup per head from the pooled logits on, in the three selection modes, every head's
+    scores, route, direction sets and pairs against the oracle, and the prefill's lists (p_v
+    and p_s formed inside the selection) equal to the stage-by-stage calls'."""
+    C = _crisp()
+    _say(f"mid-size selection n={n} B={block} {mode}")
+    cfg = custom_config(n, 4, 2, block=block, config_id=190 + n % 7, diffuse_frac=0.5)
+    params = {"floor": C.make_params(alpha=0.8), "median": C.make_params(floor_mode=C.FLOOR_MEDIAN),
+              "flex": C.flexprefill_params()}[mode]
+    _check_layer(C, cfg, params, qbs_per_head=lambda h, nb: [0, nb - 1], where=f"mid n{n} {mode}")
+    q, k, v, _ = make_layer(cfg, device=DEV)
+    _, _, _, route, rp, ci, _ = _run_stages(C, q, k, v, params, block)
+    _, r2, rp2, ci2 = C.crisp_prefill_attn(q, k, v, params, block, return_lists=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(r2.cpu().numpy(), route) and np.array_equal(rp2.cpu().numpy(), rp)
+    nb = O.n_blocks(n, block)
+    for h in range(4):
+        assert PR.csr_to_sets(rp2.cpu().numpy(), ci2.cpu().numpy(), h, nb) == PR.csr_to_sets(rp, ci, h, nb)
+
+
 @pytest.mark.parametrize("n,hq,hkv,block", [(8192, 16, 4, 64), (6000, 24, 8, 128)])
 def test_short_layer_one_workgroup_per_unit(n, hq, hkv, block):
     """Short layers with at least as many (head, query block) units as the persistent grid
