@@ -409,14 +409,15 @@ __global__ __launch_bounds__(1024) void sel_route_vs(SelArgs a) {
   vs_dir(a, vs, (dir == 0 ? a.p_v : a.p_s) + (size_t)h * a.nb, a.masks + at, a.dir_mask ? a.dir_mask + at : nullptr, vsh);
 }
 
-// Mean of rows [r0, r1) of a [rows][128] bf16 tensor into dst[0..128) (fp32).  256 threads.
+// Mean of rows [r0, r1) of a [rows][128] bf16 tensor into dst[0..128) (fp32), by the first
+// 256 threads of the workgroup.
 __device__ void pool_rows(const uint16_t* src, int r0, int r1, float* dst, float (*red)[128]) {
   const int tid = threadIdx.x;
   const int c = tid & 15, rg = tid >> 4;
   float acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-  for (int r = r0 + rg; r < r1; r += 16) {
+  for (int r = r0 + rg; rg < 16 && r < r1; r += 16) {
     const u32x4 raw = *reinterpret_cast<const u32x4*>(src + (size_t)r * kHeadDim + 8 * c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -424,8 +425,10 @@ __device__ void pool_rows(const uint16_t* src, int r0, int r1, float* dst, float
       acc[2 * e + 1] += __uint_as_float(raw[e] & 0xffff0000u);
     }
   }
+  if (rg < 16) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[rg][8 * c + e] = acc[e];
+    for (int e = 0; e < 8; ++e) red[rg][8 * c + e] = acc[e];
+  }
   __syncthreads();
   if (tid < 128) {
     float s = 0.f;
@@ -485,19 +488,21 @@ __device__ double block_sum_256d(double x, double* red) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
   const int tid = threadIdx.x;
-  if ((tid & 63) == 0) red[tid >> 6] = x;
+  if ((tid & 63) == 0 && tid < 256) red[tid >> 6] = x;
   __syncthreads();
   const double s = (red[0] + red[1]) + (red[2] + red[3]);
   __syncthreads();
   return s;
 }
 
-// One query head per workgroup, 256 threads: pooled last query block, logits
-// against K_bar (one wave per key block), softmax and the two KL terms in fp64.
-__global__ __launch_bounds__(256) void jsd_score(JsdArgs a) {
+// One query head per workgroup, 1024 threads: pooled last query block, logits against K_bar
+// (one wave per key block, eight blocks' rows in flight: the loop is bound by their latency;
+// at 128 blocks four waves and one row at a time took 22.0 us, this 8.9), softmax
+// and the two KL terms in fp64 on the first 256 threads.
+__global__ __launch_bounds__(1024) void jsd_score(JsdArgs a) {
   __shared__ float red[16][128];
   __shared__ float qm[128];
-  __shared__ float fred[4];
+  __shared__ float fred[16];
   __shared__ double dred[4];
   const int h = blockIdx.x, g = h / a.G, tid = threadIdx.x, l = tid & 63, w = tid >> 6;
   pool_rows(a.q + (size_t)h * a.n * kHeadDim, a.n - a.b, a.n, qm, red);
@@ -506,21 +511,32 @@ __global__ __launch_bounds__(256) void jsd_score(JsdArgs a) {
   float* z = a.zbuf + (size_t)h * a.nb;
   const float q0 = qm[2 * l], q1 = qm[2 * l + 1];
   float mx = -__builtin_inff();
-  for (int J = w; J < a.nb; J += 4) {
-    const float* kr = kb + (size_t)J * kHeadDim + 2 * l;
-    const float d = wave_sum(q0 * kr[0] + q1 * kr[1]) * a.scale;
-    if (l == 0) z[J] = d;
-    mx = fmaxf(mx, d);
+  for (int J0 = w; J0 < a.nb; J0 += 128) {
+    float2 kr[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int J = J0 + 16 * x;
+      kr[x] = *reinterpret_cast<const float2*>(kb + (size_t)(J < a.nb ? J : 0) * kHeadDim + 2 * l);
+    }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int J = J0 + 16 * x;
+      if (J >= a.nb) break;
+      const float d = wave_sum(q0 * kr[x].x + q1 * kr[x].y) * a.scale;
+      if (l == 0) z[J] = d;
+      mx = fmaxf(mx, d);
+    }
   }
   if (l == 0) fred[w] = mx;
   __syncthreads();  // also publishes the z written by lane 0 of every wave
-  mx = fmaxf(fmaxf(fred[0], fred[1]), fmaxf(fred[2], fred[3]));
+  for (int i = 0; i < 16; ++i) mx = fmaxf(mx, fred[i]);
   double s = 0.0;
-  for (int J = tid; J < a.nb; J += 256) s += (double)expf(z[J] - mx);
+  if (tid < 256)
+    for (int J = tid; J < a.nb; J += 256) s += (double)expf(z[J] - mx);
   s = block_sum_256d(s, dred);
   double t = 0.0;
   const float* pv = a.p_v + (size_t)h * a.nb;
-  for (int J = tid; J < a.nb; J += 256) {
+  for (int J = tid; tid < 256 && J < a.nb; J += 256) {
     const double ab = (double)expf(z[J] - mx) / s;
     const double ah = (double)pv[J];
     const double m = 0.5 * (ah + ab);
@@ -1666,7 +1682,7 @@ hipError_t launch_jsd(const Dims& d, float scale, const uint16_t* q, const uint1
   a.n = d.n; a.nb = d.nb; a.B = d.B; a.b = d.b; a.hq = d.hq; a.hkv = d.hkv; a.G = d.G;
   a.scale = scale;
   hipLaunchKernelGGL(jsd_pool_k, dim3(d.nb, d.hkv), dim3(256), 0, stream, a);
-  hipLaunchKernelGGL(jsd_score, dim3(d.hq), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(jsd_score, dim3(d.hq), dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
 
