@@ -440,16 +440,21 @@ crisp_status crisp_prefill_attn(const crisp_shape* shape, const crisp_params* pa
   const float scale = scale_of(params->softmax_scale);
   hipStream_t st = (hipStream_t)stream;
   const bool by_jsd = params->route_mode == CRISP_ROUTE_BY_JSD;
-  // Short and mid-size layers: the selection forms p_v and p_s itself from the estimator's sums (one
-  // launch fewer); the pattern search reads p_v, so it keeps the estimator's own step.
-  const bool fold = !by_jsd && d.nb <= kFoldBlocks;
-  CHECK(hip_status(launch_estimate(d, scale, params->w_sink, params->w_local, q, k, cs, pv, ps, ws, st, fold),
+  // Short and mid-size layers: the selection forms p_v and p_s itself from the estimator's
+  // sums (one launch fewer), the shortest also C_struct, with the pooling beside the pass; the
+  // pattern search reads p_v, so it keeps the estimator's own steps.
+  const bool beside = (int64_t)d.hq * d.n <= kPoolBesideRows;
+  const EstTail tail = by_jsd || d.nb > kFoldBlocks ? EstTail::kScores
+                       : !beside                    ? EstTail::kCombine
+                       : d.nb > kSmallSelectBlocks  ? EstTail::kCombinePool
+                                                    : EstTail::kPool;
+  CHECK(hip_status(launch_estimate(d, scale, params->w_sink, params->w_local, q, k, cs, pv, ps, ws, st, tail),
                    "crisp_prefill_attn estimate launch"));
   if (by_jsd)  // the route score slot then holds D_JS instead of C_struct
     CHECK(hip_status(launch_jsd(d, scale, q, k, pv, cs, ws, st), "crisp_prefill_attn pattern search launch"));
   CHECK(hip_status(launch_select(d, scale, params->alpha, route_tau(params), params->gamma, kmin_of(params, d.B),
                                  params->vs_mode, params->floor_mode, by_jsd, q, k, cs, pv, ps, route, rp, ci,
-                                 d.cap, nullptr, ws, st, fold),
+                                 d.cap, nullptr, ws, st, tail),
                    "crisp_prefill_attn select launch"));
   return hip_status(launch_attn(d, scale, q, k, v, rp, ci, d.cap, false, o, ws + L.sched, st),
                     "crisp_prefill_attn attention launch");

@@ -169,6 +169,80 @@ __device__ __forceinline__ void proxy_row_sums(float4 e0, float4 e1, float c, fl
   *slo = wave_sum(lo0 + lo1);
   *shi = wave_sum(hi0 + hi1);
 }
+// Mean of rows [r0, r1) of a [rows][128] bf16 tensor into dst[0..128) (fp32), by the first
+// 256 threads of the workgroup.
+__device__ inline void pool_rows(const uint16_t* src, int r0, int r1, float* dst, float (*red)[128]) {
+  const int tid = threadIdx.x;
+  const int c = tid & 15, rg = tid >> 4;
+  float acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  for (int r = r0 + rg; rg < 16 && r < r1; r += 16) {
+    const u32x4 raw = *reinterpret_cast<const u32x4*>(src + (size_t)r * kHeadDim + 8 * c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc[2 * e] += __uint_as_float(raw[e] << 16);
+      acc[2 * e + 1] += __uint_as_float(raw[e] & 0xffff0000u);
+    }
+  }
+  if (rg < 16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[rg][8 * c + e] = acc[e];
+  }
+  __syncthreads();
+  if (tid < 128) {
+    float s = 0.f;
+    for (int i = 0; i < 16; ++i) s += red[i][tid];
+    dst[tid] = s / (float)(r1 - r0);
+  }
+}
+
+// Merges a range's (max m, sums l and anchor under m) into a running (M, L, A).
+__device__ __forceinline__ void merge_stats(float& M, float& L, float& A, float m, float l, float anc, float c) {
+  if (m == -__builtin_inff()) return;
+  if (m > M) {
+    const float f = M == -__builtin_inff() ? 0.f : fast_exp2((M - m) * c);
+    L = L * f + l;
+    A = A * f + anc;
+    M = m;
+  } else {
+    const float f = fast_exp2((m - M) * c);
+    L += l * f;
+    A += anc * f;
+  }
+}
+
+// Per query head: each proxy row's max M and sum L over all ranges (eight lanes per
+// row, each merging every eighth range in one pass, then a fixed-order butterfly),
+// the row's normaliser mcl = M c + log2 L for the block sums (128 floats at rowfinal), and
+// C_struct = (1/b) sum over rows of the row's anchor mass / L, summed over rows in a fixed
+// order, returned to wave 0.  rowstat: the head's [splits][128] statistics; red: 128
+// floats of LDS.  1024 threads.
+__device__ __forceinline__ float combine_head(const float4* rowstat, int splits, int b, float c, float* rowfinal, float* red) {
+  const int j = threadIdx.x & 7, r = threadIdx.x >> 3;
+  const float4* src = rowstat + r;
+  const bool row_ok = r < b;
+  float M = -__builtin_inff(), L = 0.f, A = 0.f;
+  if (row_ok)
+    for (int sp = j; sp < splits; sp += 8) {
+      const float4 st = src[(size_t)sp * 128];
+      merge_stats(M, L, A, st.x, st.y, st.z, c);
+    }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    const float m2 = __shfl_xor(M, o, 64), l2 = __shfl_xor(L, o, 64), a2 = __shfl_xor(A, o, 64);
+    merge_stats(M, L, A, m2, l2, a2, c);
+  }
+  if (j == 0) {
+    rowfinal[r] = row_ok ? M * c + log2f(L) : __builtin_inff();
+    red[r] = row_ok ? A / L : 0.f;
+  }
+  __syncthreads();
+  float t = 0.f;
+  if (threadIdx.x < 64) t = wave_sum(red[threadIdx.x] + red[threadIdx.x + 64]) / (float)b;
+  return t;
+}
+
 #if defined(__HIP_DEVICE_COMPILE__)
 
 // Tile fetch: a 64-key x 128-dim tile goes straight from global memory into an

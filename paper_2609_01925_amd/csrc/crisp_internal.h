@@ -49,27 +49,37 @@ hipError_t launch_attn(const Dims& d, float scale, const uint16_t* q, const uint
                        const int32_t* row_ptr, const int32_t* col_idx, int64_t col_cap, bool dense,
                        uint16_t* o, void* sched, hipStream_t stream, int max_slots = kWorkspaceSlots);
 
-// combine_only: C_struct and the per-row normalisers only; p_v and p_s stay unwritten
-// (launch_select with scores_from_ws forms them from the workspace instead).
+// What the estimator leaves to launch_select, which then takes it from the workspace: kScores
+// nothing (C_struct, p_v and p_s are written); kCombine p_v and p_s (C_struct and the per-row
+// normalisers are written; layers of at most kFoldBlocks blocks).  kCombinePool: as kCombine,
+// and the block means of all Q heads and KV groups were made beside the pass; kPool: C_struct
+// is left as well (layers of at most kSmallSelectBlocks blocks).
+enum class EstTail { kScores, kCombine, kCombinePool, kPool };
 hipError_t launch_estimate(const Dims& d, float scale, int w_sink, int w_local, const uint16_t* q,
                            const uint16_t* k, float* c_struct, float* p_v, float* p_s, char* ws,
-                           hipStream_t stream, bool combine_only = false);
+                           hipStream_t stream, EstTail tail = EstTail::kScores);
 
 // Layers of at most this many blocks take the one-launch-per-head selection.
 constexpr int kSmallSelectBlocks = 64;
 // Up to this many blocks one workgroup per head selects from the pooled logits on, and in
 // prefill forms the head's p_v and p_s from the estimator's sums.
 constexpr int kFoldBlocks = 256;
+// Up to this many query rows (heads x tokens) the pooling runs beside the estimator's pass,
+// for every head (the routes are not known yet), and up to kSmallSelectBlocks blocks the
+// combine inside the selection.  That saves one or two launches for the pooling of the VS
+// heads' Q, which passes under the pass while Q is small.  Whole prefill without -> with: 4k
+// tokens, 2 heads 72.2 -> 67.1 us; 32 heads at 2k 70.5 -> 65.0, 4k 116.4 -> 111.8, 8k (the
+// limit) 256.2 -> 249.7; 28 heads at 5k, 64-row blocks 191.1 -> 187.0.
+constexpr int64_t kPoolBesideRows = 262144;
 
 // route_score is C_struct (tau = tau_proxy) or D_JS (tau = tau_jsd); vs_mode 0 is the
 // noise floor (floor_mode 0: mean, 1: median), 1 gamma coverage; kbar_all: K_bar of
-// every KV group is already in ws.  scores_from_ws (layers of at most kFoldBlocks
-// blocks, after launch_estimate with combine_only on the same ws): p_v and p_s are not
-// read; the selection forms them from the estimator's sums in ws.
+// every KV group is already in ws.  tail: what launch_estimate on the same
+// ws left to this call (route_score, p_v or p_s are then not read).
 hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, float gamma, int k_min, int vs_mode,
                          int floor_mode, bool kbar_all, const uint16_t* q, const uint16_t* k, const float* route_score,
                          const float* p_v, const float* p_s, int8_t* route, int32_t* row_ptr, int32_t* col_idx,
-                         int64_t col_cap, uint8_t* dir_mask, char* ws, hipStream_t stream, bool scores_from_ws = false);
+                         int64_t col_cap, uint8_t* dir_mask, char* ws, hipStream_t stream, EstTail tail = EstTail::kScores);
 
 // route = dense and full causal CSR lists (col_cap >= nb (nb + 1) / 2).
 hipError_t launch_dense_lists(const Dims& d, int8_t* route, int32_t* row_ptr, int32_t* col_idx, int64_t col_cap,

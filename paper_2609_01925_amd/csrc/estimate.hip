@@ -38,6 +38,9 @@ struct EstArgs {
   float* c_struct;
   float* p_v;
   float* p_s;
+  int pass_grid;  // workgroups of the pass; those from it on pool Q and K (below)
+  float* qbar;    // [hq][nb][128], [hkv][nb][128] block means, when they do
+  float* kbar;
 };
 
 __device__ __forceinline__ void load_q_hat(const EstArgs& a, int h, int r, int l, bf16x8 (&qf)[8]) {
@@ -93,6 +96,18 @@ __device__ __forceinline__ int key_of(int key0, int mb, int i, int l) {
 __global__ __launch_bounds__(NT, 4) void est_pass(EstArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) char smem[2 * kTileBytes];
+  if ((int)blockIdx.x >= a.pass_grid) {
+    // Short and few-head layers in prefill: workgroups after the pass's mean-pool every block of every
+    // query head and KV group in the same launch (Alg. 4 needs those of PE heads only, but
+    // the routes are not known yet), so that no launch stands between the pass and the
+    // selection.
+    const int i = blockIdx.x - a.pass_grid, J = i % a.nb, y = i / a.nb, g = y - a.hq, r0 = J * a.B;
+    pool_rows(g < 0 ? a.q + (size_t)y * a.n * kHeadDim : a.k + (size_t)g * a.n * kHeadDim, r0,
+              r0 + a.B < a.n ? r0 + a.B : a.n,
+              g < 0 ? a.qbar + ((size_t)y * a.nb + J) * kHeadDim : a.kbar + ((size_t)g * a.nb + J) * kHeadDim,
+              reinterpret_cast<float(*)[128]>(smem));
+    return;
+  }
   const int lds0 = __builtin_amdgcn_readfirstlane((int)(size_t)smem);
   // Workgroup i runs on XCD i % 8.  The G query heads of one (KV group, key range) take
   // consecutive workgroups of one XCD, so they stream the same K tiles through that
@@ -242,56 +257,11 @@ __global__ __launch_bounds__(NT, 4) void est_pass(EstArgs a) {
 #endif
 }
 
-// Merges a range's (max m, sums l and anchor under m) into a running (M, L, A).
-__device__ __forceinline__ void merge_stats(float& M, float& L, float& A, float m, float l, float anc, float c) {
-  if (m == -__builtin_inff()) return;
-  if (m > M) {
-    const float f = M == -__builtin_inff() ? 0.f : fast_exp2((M - m) * c);
-    L = L * f + l;
-    A = A * f + anc;
-    M = m;
-  } else {
-    const float f = fast_exp2((m - M) * c);
-    L += l * f;
-    A += anc * f;
-  }
-}
-
-// Per query head: each proxy row's max M and sum L over all ranges (eight lanes per
-// row, each merging every eighth range in one pass, then a fixed-order butterfly),
-// the row's normaliser mcl = M c + log2 L for the block sums, and C_struct = (1/b)
-// sum over rows of the row's anchor mass / L, summed over rows in a fixed order.
-// 1024 threads.
-__device__ __forceinline__ void combine_head(const EstArgs& a, int h, float* red) {
-  const int j = threadIdx.x & 7, r = threadIdx.x >> 3;
-  const float4* src = a.rowstat + (size_t)h * a.splits * 128 + r;
-  const bool row_ok = r < a.b;
-  float M = -__builtin_inff(), L = 0.f, A = 0.f;
-  if (row_ok)
-    for (int sp = j; sp < a.splits; sp += 8) {
-      const float4 st = src[(size_t)sp * 128];
-      merge_stats(M, L, A, st.x, st.y, st.z, a.c);
-    }
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) {
-    const float m2 = __shfl_xor(M, o, 64), l2 = __shfl_xor(L, o, 64), a2 = __shfl_xor(A, o, 64);
-    merge_stats(M, L, A, m2, l2, a2, a.c);
-  }
-  if (j == 0) {
-    a.rowfinal[(size_t)h * 128 + r] = row_ok ? M * a.c + log2f(L) : __builtin_inff();
-    red[r] = row_ok ? A / L : 0.f;
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    float t = red[threadIdx.x] + red[threadIdx.x + 64];
-    t = wave_sum(t);
-    if (threadIdx.x == 0) a.c_struct[h] = t / (float)a.b;
-  }
-}
-
 __global__ __launch_bounds__(1024) void est_combine(EstArgs a) {
   __shared__ float red[128];
-  combine_head(a, blockIdx.x, red);
+  const int h = blockIdx.x;
+  const float cs = combine_head(a.rowstat + (size_t)h * a.splits * 128, a.splits, a.b, a.c, a.rowfinal + (size_t)h * 128, red);
+  if (threadIdx.x == 0) a.c_struct[h] = cs;
 }
 
 constexpr int kScaleRun = 2;
@@ -347,7 +317,8 @@ constexpr int kFinishSmall = 32;
 __global__ __launch_bounds__(1024) void est_finish(EstArgs a) {
   __shared__ float red[128];
   const int h = blockIdx.x;
-  combine_head(a, h, red);
+  const float cs = combine_head(a.rowstat + (size_t)h * a.splits * 128, a.splits, a.b, a.c, a.rowfinal + (size_t)h * 128, red);
+  if (threadIdx.x == 0) a.c_struct[h] = cs;
   __syncthreads();  // rowfinal of every row is visible to the whole workgroup
   for (int Ja = (threadIdx.x >> 6) * kScaleRun; Ja < a.nb; Ja += 16 * kScaleRun)
     scale_run(a, h, Ja, Ja + kScaleRun < a.nb ? Ja + kScaleRun : a.nb);
@@ -375,7 +346,7 @@ EstSplit est_split(const Dims& d) {
 
 hipError_t launch_estimate(const Dims& d, float scale, int w_sink, int w_local, const uint16_t* q,
                            const uint16_t* k, float* c_struct, float* p_v, float* p_s, char* ws,
-                           hipStream_t stream, bool combine_only) {
+                           hipStream_t stream, EstTail tail) {
   if (d.n == 0 || d.hq == 0) return hipSuccess;
   const WsLayout L = ws_layout(d);
   const EstSplit sp = est_split(d);
@@ -391,8 +362,13 @@ hipError_t launch_estimate(const Dims& d, float scale, int w_sink, int w_local, 
   a.c_struct = c_struct; a.p_v = p_v; a.p_s = p_s;
   const int pairs = d.hkv * sp.splits;  // (KV group, key range) pairs, spread over the XCDs
   const int grid = kNumXcd * d.G * ((pairs + kNumXcd - 1) / kNumXcd);
-  hipLaunchKernelGGL(est_pass, dim3(grid), dim3(NT), 0, stream, a);
-  if (combine_only) {  // p_v and p_s are left to the caller's next launch (from parts and rowfinal)
+  a.pass_grid = grid;
+  a.qbar = reinterpret_cast<float*>(ws + L.qbar);
+  a.kbar = reinterpret_cast<float*>(ws + L.kbar);
+  const bool pool = tail == EstTail::kPool || tail == EstTail::kCombinePool;
+  hipLaunchKernelGGL(est_pass, dim3(grid + (pool ? d.nb * (d.hq + d.hkv) : 0)), dim3(NT), 0, stream, a);
+  if (tail == EstTail::kPool) return hipGetLastError();  // the caller's next launch combines, too
+  if (tail != EstTail::kScores) {  // p_v and p_s are left to the caller's next launch (from parts and rowfinal)
     hipLaunchKernelGGL(est_combine, dim3(d.hq), dim3(1024), 0, stream, a);
   } else if (d.nb <= kFinishSmall) {
     hipLaunchKernelGGL(est_finish, dim3(d.hq), dim3(1024), 0, stream, a);

@@ -68,7 +68,9 @@ struct SelArgs {
   RState* rstate;
   int4* rowinfo;
   const float4* parts;     // short layers from prefill: the estimator's per-(block, row) sums, else null
-  const float* rowfinal;   // their per-row normalisers
+  const float* rowfinal;   // their per-row normalisers, or null:
+  const float4* rowstat;   // the ranges' row statistics [hq][splits][128] to combine first
+  int splits;
   int b;                   // proxy rows
 };
 
@@ -407,34 +409,6 @@ __global__ __launch_bounds__(1024) void sel_route_vs(SelArgs a) {
   if (dir == 0 && threadIdx.x == 0) a.route[h] = vs ? 0 : 1;
   const size_t at = ((size_t)h * 2 + dir) * a.nb;
   vs_dir(a, vs, (dir == 0 ? a.p_v : a.p_s) + (size_t)h * a.nb, a.masks + at, a.dir_mask ? a.dir_mask + at : nullptr, vsh);
-}
-
-// Mean of rows [r0, r1) of a [rows][128] bf16 tensor into dst[0..128) (fp32), by the first
-// 256 threads of the workgroup.
-__device__ void pool_rows(const uint16_t* src, int r0, int r1, float* dst, float (*red)[128]) {
-  const int tid = threadIdx.x;
-  const int c = tid & 15, rg = tid >> 4;
-  float acc[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-  for (int r = r0 + rg; rg < 16 && r < r1; r += 16) {
-    const u32x4 raw = *reinterpret_cast<const u32x4*>(src + (size_t)r * kHeadDim + 8 * c);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[2 * e] += __uint_as_float(raw[e] << 16);
-      acc[2 * e + 1] += __uint_as_float(raw[e] & 0xffff0000u);
-    }
-  }
-  if (rg < 16) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) red[rg][8 * c + e] = acc[e];
-  }
-  __syncthreads();
-  if (tid < 128) {
-    float s = 0.f;
-    for (int i = 0; i < 16; ++i) s += red[i][tid];
-    dst[tid] = s / (float)(r1 - r0);
-  }
 }
 
 // Mean-pool Q of PE heads and K of KV groups with a PE head (Alg. 4).  grid (nb, hq + hkv), 256 threads.
@@ -1188,11 +1162,11 @@ __global__ __launch_bounds__(256) void sel_csr_fill(SelArgs a) {
 // them: p_v[J] = (lo[J] + hi[J]) / b, p_s[J] = (lo[J] + hi[J - 1]) / b, every sum in the same
 // order.  1024 threads; bsum and pvs hold 2 x NB floats each.
 template <int NB>
-__device__ __forceinline__ void scores_from_parts(const SelArgs& a, int h, float (*bsum)[NB], float (*pvs)[NB]) {
+__device__ __forceinline__ void scores_from_parts(const SelArgs& a, int h, const float* mcl, float (*bsum)[NB], float (*pvs)[NB]) {
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, nb = a.nb;
   const bool ok0 = l < a.b, ok1 = l + 64 < a.b;
-  const float mcl0 = ok0 ? a.rowfinal[(size_t)h * 128 + l] : 0.f;
-  const float mcl1 = ok1 ? a.rowfinal[(size_t)h * 128 + l + 64] : 0.f;
+  const float mcl0 = ok0 ? mcl[l] : 0.f;
+  const float mcl1 = ok1 ? mcl[l + 64] : 0.f;
   const float4* P = a.parts + (size_t)h * nb * 128;
   for (int J0 = w; J0 < nb; J0 += 64) {  // four blocks of this wave, their loads in flight together
     const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1365,7 +1339,7 @@ __global__ __launch_bounds__(1024) void sel_mid(SelArgs a) {
   if (vs) {
     const float* p[2] = {a.p_v + (size_t)h * nb, a.p_s + (size_t)h * nb};
     if (a.parts) {
-      scores_from_parts<kMidBlocks>(a, h, sm.bsum, sm.pvs);
+      scores_from_parts<kMidBlocks>(a, h, a.rowfinal + (size_t)h * 128, sm.bsum, sm.pvs);
       p[0] = sm.pvs[0];
       p[1] = sm.pvs[1];
     }
@@ -1534,17 +1508,28 @@ struct SmallShared {
   RState st;
   float bsum[2][kPeSmall];  // per block: the proxy's lo and hi mass summed over rows
   float pvs[2][kPeSmall];   // p_v and p_s of the head
+  float mcl[128], red[128];  // the proxy rows' normalisers, when they are combined here
+  float score;
 };
 
 __global__ __launch_bounds__(kSmallThreads) void sel_small(SelArgs a) {
   __shared__ __attribute__((aligned(16))) SmallShared sm;
   const int h = blockIdx.x, tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int nb = a.nb;
-  const bool vs = a.c_struct[h] >= a.tau;
+  float score;
+  if (a.rowstat) {
+    const float cs = combine_head(a.rowstat + (size_t)h * a.splits * 128, a.splits, a.b, a.c2, sm.mcl, sm.red);
+    if (tid == 0) sm.score = cs;
+    __syncthreads();
+    score = sm.score;
+  } else {
+    score = a.c_struct[h];
+  }
+  const bool vs = score >= a.tau;
   if (tid == 0) a.route[h] = vs ? 0 : 1;
   const float* pdir[2] = {a.p_v + (size_t)h * nb, a.p_s + (size_t)h * nb};
   if (vs && a.parts) {
-    scores_from_parts<kPeSmall>(a, h, sm.bsum, sm.pvs);
+    scores_from_parts<kPeSmall>(a, h, a.rowfinal ? a.rowfinal + (size_t)h * 128 : sm.mcl, sm.bsum, sm.pvs);
     pdir[0] = sm.pvs[0];
     pdir[1] = sm.pvs[1];
   }
@@ -1689,7 +1674,7 @@ hipError_t launch_jsd(const Dims& d, float scale, const uint16_t* q, const uint1
 hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, float gamma, int k_min, int vs_mode,
                          int floor_mode, bool kbar_all, const uint16_t* q, const uint16_t* k, const float* route_score,
                          const float* p_v, const float* p_s, int8_t* route, int32_t* row_ptr, int32_t* col_idx,
-                         int64_t col_cap, uint8_t* dir_mask, char* ws, hipStream_t stream, bool scores_from_ws) {
+                         int64_t col_cap, uint8_t* dir_mask, char* ws, hipStream_t stream, EstTail tail) {
   if (d.n == 0 || d.hq == 0) return hipSuccess;
   const WsLayout L = ws_layout(d);
   SelArgs a;
@@ -1708,18 +1693,19 @@ hipError_t launch_select(const Dims& d, float scale, float alpha, float tau, flo
   a.rstate = reinterpret_cast<RState*>(ws + L.rstate);
   a.rowinfo = reinterpret_cast<int4*>(ws + L.rowinfo);
   const int nb = d.nb;
-  const bool from_ws = scores_from_ws && nb <= kFoldBlocks;
-  a.parts = from_ws ? reinterpret_cast<const float4*>(ws + L.parts) : nullptr;
-  a.rowfinal = from_ws ? reinterpret_cast<const float*>(ws + L.rowfinal) : nullptr;
+  a.parts = tail != EstTail::kScores ? reinterpret_cast<const float4*>(ws + L.parts) : nullptr;
+  a.rowfinal = tail == EstTail::kCombine || tail == EstTail::kCombinePool ? reinterpret_cast<const float*>(ws + L.rowfinal) : nullptr;
+  a.rowstat = tail == EstTail::kPool ? reinterpret_cast<const float4*>(ws + L.rowstat) : nullptr;
+  a.splits = est_split(d).splits;
   a.b = d.b;
   if (nb <= kPeSmall) {  // short layers: pooling, then the whole selection in one launch per head
-    hipLaunchKernelGGL(sel_pool, dim3(nb, d.hq + d.hkv), dim3(256), 0, stream, a);
+    if (tail != EstTail::kPool) hipLaunchKernelGGL(sel_pool, dim3(nb, d.hq + d.hkv), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sel_small, dim3(d.hq), dim3(kSmallThreads), 0, stream, a);
     return hipGetLastError();
   }
   const bool mid = nb <= kMidBlocks;
   if (!mid) hipLaunchKernelGGL(sel_route_vs, dim3(d.hq, 2), dim3(1024), 0, stream, a);
-  hipLaunchKernelGGL(sel_pool, dim3(nb, d.hq + d.hkv), dim3(256), 0, stream, a);
+  if (tail != EstTail::kCombinePool) hipLaunchKernelGGL(sel_pool, dim3(nb, d.hq + d.hkv), dim3(256), 0, stream, a);
   if (nb <= kLogitDirect) {
     const int nt = (nb + 63) / 64;
     hipLaunchKernelGGL(sel_pe_logits_direct, dim3(nt * (nt + 1) / 2, d.hq), dim3(256), 0, stream, a);
