@@ -754,8 +754,10 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
 // ceil(L / C) chunks, each a work item of its own that leaves a partial result
 // in a slot or merges its sibling's (attn_unit).  Chunks number at most
 // T / C + (rows longer than C) <= 2 G' <= slots.  When that bound on the slots and not
-// the grid sets C (few units), the C of the whole grid is tried first and taken if its
-// chunks fit the slots.  The decision depends only on the lists and the grid, so results
+// the grid sets C (few units), 5/4 of the grid's ceil(T / grid) is tried first and taken if
+// its chunks fit the slots (whole prefill, us, C from 1x / 5/4 / 3/2 of it / the bound
+// alone: 24k tokens, 8 heads, 64-row blocks 671 / 690 / 751 / 761; 12k, 16 heads, structured
+// heads 407 / 387 / 386 / 386: at 1x nearly every long row is split).  The decision depends only on the lists and the grid, so results
 // do not depend on timing.
 //
 // One workgroup builds everything and resets the queue and arrival counters; the order
@@ -864,7 +866,7 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
     gp = a.grid < gp ? a.grid : gp;
     gp = gp < 1 ? 1 : gp;
     long long c = chunk_for(gp);
-    const int cg = (int)chunk_for(a.grid);
+    const int cg = (int)chunk_for((long long)a.grid * 4 / 5);
     if (cg < c && s_max > cg) {
       int chunks = 0;
       each_unit([&](int, int L) { chunks += L > cg ? (L + cg - 1) / cg : 0; });
