@@ -264,7 +264,11 @@ __global__ __launch_bounds__(1024) void est_combine(EstArgs a) {
   if (threadIdx.x == 0) a.c_struct[h] = cs;
 }
 
-constexpr int kScaleRun = 2;
+// Blocks per wave of the scale: latency-bound (64k tokens, 32 heads: 9.0 -> 7.1 us with a run's
+// loads in flight together; 2, 3 and 4 blocks alike), and at 128k its reads of parts count, of
+// which one in kScaleRun + 1 is the block before the run: the whole estimator 202.6 / 203.9 /
+// 199.5 us with 2 / 3 / 4.
+constexpr int kScaleRun = 4;
 
 // p_v[J] = (1/b) sum_r (lo + hi)[r][J] 2^(m c - mcl_r);  p_s[J] = (1/b) sum_r (lo[r][J] +
 // hi[r][J - 1]) scaled alike, for the run of blocks [Ja, Jb) (at most kScaleRun) of head h, by one wave:
@@ -274,38 +278,35 @@ __device__ __forceinline__ void scale_run(const EstArgs& a, int h, int Ja, int J
   const bool ok0 = l < a.b, ok1 = l + 64 < a.b;
   const float mcl0 = ok0 ? a.rowfinal[(size_t)h * 128 + l] : 0.f;
   const float mcl1 = ok1 ? a.rowfinal[(size_t)h * 128 + l + 64] : 0.f;
-  // the run's blocks and the one before it, all their loads in flight together (one memory
-  // latency per run)
+  // The run's blocks and the one before it, all their loads in flight together (one memory
+  // latency per run).  The loads are whole and unconditional: a block outside the layer is
+  // clamped to one inside, whose sums nothing takes, and rows from b to 127 have a place in parts.
   const float4* P = a.parts + (size_t)h * a.nb * 128;
-  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
   float4 e0[kScaleRun + 1], e1[kScaleRun + 1];
 #pragma unroll
   for (int x = 0; x <= kScaleRun; ++x) {
-    const int J = Ja - 1 + x;
-    const bool in = J >= 0 && J < Jb;
-    e0[x] = in && ok0 ? P[(size_t)J * 128 + l] : z;
-    e1[x] = in && ok1 ? P[(size_t)J * 128 + l + 64] : z;
+    const int J = Ja - 1 + x < 0 ? 0 : Ja - 1 + x < Jb ? Ja - 1 + x : Jb - 1;
+    e0[x] = P[(size_t)J * 128 + l];
+    e1[x] = P[(size_t)J * 128 + l + 64];
   }
   float prev_hi = 0.f;
   const float invb = 1.f / (float)a.b;
 #pragma unroll
   for (int x = 0; x <= kScaleRun; ++x) {
     const int J = Ja - 1 + x;
-    if (J < 0) continue;
-    if (J >= Jb) break;
     float slo, shi;
     proxy_row_sums(e0[x], e1[x], a.c, mcl0, mcl1, ok0, ok1, &slo, &shi);
-    if (x > 0 && l == 0) {
+    if (x > 0 && J < Jb && l == 0) {
       a.p_v[(size_t)h * a.nb + J] = (slo + shi) * invb;
       a.p_s[(size_t)h * a.nb + J] = (slo + prev_hi) * invb;
     }
-    prev_hi = shi;
+    prev_hi = J < 0 ? 0.f : shi;
   }
 }
 
 // Each wave takes kScaleRun consecutive blocks.  grid (hq, ceil(runs / 4)), 256 threads.
 __global__ __launch_bounds__(256) void est_scale(EstArgs a) {
-  const int Ja = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kScaleRun;
+  const int Ja = __builtin_amdgcn_readfirstlane((blockIdx.y * 4 + (threadIdx.x >> 6)) * kScaleRun);
   if (Ja >= a.nb) return;
   scale_run(a, blockIdx.x, Ja, Ja + kScaleRun < a.nb ? Ja + kScaleRun : a.nb);
 }

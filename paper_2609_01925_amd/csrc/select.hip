@@ -1163,19 +1163,18 @@ __global__ __launch_bounds__(256) void sel_csr_fill(SelArgs a) {
 // order.  1024 threads; bsum and pvs hold 2 x NB floats each.
 template <int NB>
 __device__ __forceinline__ void scores_from_parts(const SelArgs& a, int h, const float* mcl, float (*bsum)[NB], float (*pvs)[NB]) {
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, nb = a.nb;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, nb = a.nb;
   const bool ok0 = l < a.b, ok1 = l + 64 < a.b;
   const float mcl0 = ok0 ? mcl[l] : 0.f;
   const float mcl1 = ok1 ? mcl[l + 64] : 0.f;
   const float4* P = a.parts + (size_t)h * nb * 128;
   for (int J0 = w; J0 < nb; J0 += 64) {  // four blocks of this wave, their loads in flight together
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 e0[4], e1[4];
+    float4 e0[4], e1[4];       // whole and unconditional: past the last block they are clamped to it
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      const int J = J0 + 16 * x;
-      e0[x] = ok0 && J < nb ? P[(size_t)J * 128 + l] : z;
-      e1[x] = ok1 && J < nb ? P[(size_t)J * 128 + l + 64] : z;
+      const int J = J0 + 16 * x < nb ? J0 + 16 * x : nb - 1;
+      e0[x] = P[(size_t)J * 128 + l];
+      e1[x] = P[(size_t)J * 128 + l + 64];
     }
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
