@@ -757,8 +757,8 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
 // the grid sets C (few units), 5/4 of the grid's ceil(T / grid) is tried first and taken if
 // its chunks fit the slots (whole prefill, us, C from 1x / 5/4 / 3/2 of it / the bound
 // alone: 24k tokens, 8 heads, 64-row blocks 671 / 690 / 751 / 761; 12k, 16 heads, structured
-// heads 407 / 387 / 386 / 386: at 1x nearly every long row is split).  The decision depends only on the lists and the grid, so results
-// do not depend on timing.
+// heads 407 / 387 / 386 / 386: at 1x nearly every long row is split).  The decision depends
+// only on the lists and the grid, so results do not depend on timing.
 //
 // One workgroup builds everything and resets the queue and arrival counters; the order
 // within one length is arbitrary (it only decides which workgroup runs an item,
@@ -794,7 +794,6 @@ __device__ __forceinline__ void for_units(const AttnArgs& a, int total, int tid,
   }
 }
 
-//
 // It is one workgroup and runs once, so latency and instruction fetch bound it, not work:
 // the row lengths are read once (in batches of eight loads) and kept in LDS, and the passes
 // are short rolled loops over them.  Kernel time with lengths re-read from memory or held

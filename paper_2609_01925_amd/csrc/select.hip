@@ -1169,7 +1169,7 @@ __device__ __forceinline__ void scores_from_parts(const SelArgs& a, int h, const
   const float mcl1 = ok1 ? mcl[l + 64] : 0.f;
   const float4* P = a.parts + (size_t)h * nb * 128;
   for (int J0 = w; J0 < nb; J0 += 64) {  // four blocks of this wave, their loads in flight together
-    float4 e0[4], e1[4];       // whole and unconditional: past the last block they are clamped to it
+    float4 e0[4], e1[4];  // whole and unconditional: past the last block they are clamped to it
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int J = J0 + 16 * x < nb ? J0 + 16 * x : nb - 1;
