@@ -331,7 +331,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(const AttnArgs& a, 
 }
 
 // One (head, query block) unit, or one chunk of a split row's list: entries
-// [chunk * csize, chunk * csize + csize) when slot0 >= 0.  The chunks of a row are merged
+// [chunk * csize, chunk * csize + csize) when slot0 >= 0.  slots: four ints in LDS, a scratch
+// word, slot0, chunk and (written here) the row's number of chunks, or null; what only the
+// merge needs waits there, not in scalar registers across the tile loop (41 -> 21 of them
+// spilled; 128k tokens 43.56 -> 43.26 ms).  The chunks of a row are merged
 // pairwise in a fixed tree over the chunk index: of two siblings, the one that ends first
 // leaves its unnormalised O, row max and row sum in its slot and is done; the other merges
 // them with its own, still in registers (O = w_a O_a + w_b O_b, l alike, w_x = 2^((m_x - M) c),
@@ -341,11 +344,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(const AttnArgs& a, 
 // knowing whether a row is split) launched for every layer, took 4.6 us without and 7.2 us
 // with split rows, and its cost had kept chunks long: attention at 4k tokens and 2 heads
 // 58.7 -> 46.0 us, at 24k tokens, 8 heads and 64-row blocks 703 -> 583 us (one workgroup
-// merging all chunks of a row in turn: 50 and 612 us).  flag: an int in LDS.
+// merging all chunks of a row in turn: 50 and 612 us).
 template <int BQ, bool DENSE>
 __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, int lds0, const Offsets& off,
-                                          const Fetch<Geo<BQ>::kWaves>& fe, int tid, int chunk = 0, int csize = 0,
-                                          int slot0 = -1, int* flag = nullptr) {
+                                          const Fetch<Geo<BQ>::kWaves>& fe, int tid, int* slots = nullptr) {
   constexpr int QH = Geo<BQ>::kQH;
   constexpr int NW = Geo<BQ>::kWaves;
   constexpr int BK = Tile<BQ>::kBK, NMB = Tile<BQ>::kNMB;
@@ -359,7 +361,7 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
   const i32x4 rk = tensor_rsrc(a.k + (size_t)g * a.n * kHeadDim, a.n);
   const i32x4 rv = tensor_rsrc(a.v + (size_t)g * a.n * kHeadDim, a.n);
 
-  int beg = 0, cnt, nchunks = 0;
+  int beg = 0, cnt;
   const int32_t* cols = nullptr;
   if (DENSE) {
     cnt = qb + 1;
@@ -372,9 +374,10 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
     beg = (int)b0;
     cnt = (int)(e0 - b0);
     cols = a.col_idx + (size_t)head * cap;
-    if (slot0 >= 0) {
-      const int lo = chunk * csize;
-      nchunks = (cnt + csize - 1) / csize;
+    if (slots != nullptr && __builtin_amdgcn_readfirstlane(slots[1]) >= 0) {
+      const int csize = __builtin_amdgcn_readfirstlane(a.counter[17]);  // chunk length of split rows
+      const int lo = __builtin_amdgcn_readfirstlane(slots[2]) * csize;
+      if (tid == 0) slots[3] = (cnt + csize - 1) / csize;
       beg += lo;
       cnt = cnt - lo < csize ? cnt - lo : csize;
     }
@@ -577,7 +580,11 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
   float l_tot[QH];
 #pragma unroll
   for (int h = 0; h < QH; ++h) l_tot[h] = half_sum(l_run[h]);
-  if (!DENSE && slot0 >= 0) {
+  if (!DENSE && slots != nullptr && __builtin_amdgcn_readfirstlane(slots[1]) >= 0) {
+    __syncthreads();  // the number of chunks is visible and every wave has taken its item
+    const int slot0 = __builtin_amdgcn_readfirstlane(slots[1]), chunk = __builtin_amdgcn_readfirstlane(slots[2]);
+    const int nchunks = __builtin_amdgcn_readfirstlane(slots[3]);
+    int* flag = slots;
     static_assert(QH == 1, "one half per wave");
     constexpr int kSlotFloats = BQ * (kHeadDim + 2);
     const __amdgpu_buffer_rsrc_t pr = parts_rsrc(a, kSlotFloats);
@@ -684,7 +691,6 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
   int* s_unit = reinterpret_cast<int*>(smem + 2 * Tile<BQ>::kRing);
   const int x0 = home_queue(a, blockIdx.x % kNumXcd);
   const int* start = a.counter + 8;
-  const int csize = a.counter[17];  // chunk length of split rows
   // Queues this workgroup has seen run dry (thread 0): they are never tried again.
   // A queue whose counter already reads past its end is skipped without an atomic
   // (a stale read only costs an extra atomic: counters never decrease).
@@ -719,16 +725,19 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
       }
       *s_unit = unit;
     }
-    __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(*s_unit);
-    if (item < 0) break;
     // items carry a chunk index only when rows may be split (fewer than 2^21 units);
     // otherwise an item is the unit itself, which may exceed 2^21
     const bool split = a.split_slots > 0;
+    if (tid == 0) {
+      const int it = *s_unit;
+      s_unit[1] = split && it >= 0 ? a.slot_base[it & ((1 << kItemUnitBits) - 1)] : -1;
+      s_unit[2] = it >> kItemUnitBits;
+    }
+    __syncthreads();
+    const int item = __builtin_amdgcn_readfirstlane(*s_unit);
+    if (item < 0) break;
     const int unit = split ? item & ((1 << kItemUnitBits) - 1) : item;
-    const int chunk = split ? item >> kItemUnitBits : 0;
-    const int slot0 = split ? a.slot_base[unit] : -1;
-    attn_unit<BQ, DENSE>(a, unit / a.nb, unit % a.nb, lds0, off, fe, tid, chunk, csize, slot0, s_unit);
+    attn_unit<BQ, DENSE>(a, unit / a.nb, unit % a.nb, lds0, off, fe, tid, s_unit);
     if (a.one_shot) break;
   }
 #endif  // __HIP_DEVICE_COMPILE__
