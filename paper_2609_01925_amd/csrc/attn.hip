@@ -629,10 +629,14 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
       const float ms = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, stat, sib, kAgentScope));
       const float ls = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, stat + 4 * BQ, sib, kAgentScope));
       const float M = fmaxf(m_run[0], ms);
-      const float wo = m_run[0] == -__builtin_inff() ? 0.f : fast_exp2((m_run[0] - M) * a.c);
-      const float ws = ms == -__builtin_inff() ? 0.f : fast_exp2((ms - M) * a.c);
+      // (without a key O is 0 x V, which an infinite V makes NaN, so it is replaced and not only weighted by 0)
+      const bool no_own = m_run[0] == -__builtin_inff(), no_sib = ms == -__builtin_inff();
+      const float wo = no_own ? 0.f : fast_exp2((m_run[0] - M) * a.c);
+      const float ws = no_sib ? 0.f : fast_exp2((ms - M) * a.c);
       // left w_left + right w_right, rounded the same whichever of the two merges
       auto merged = [&](float own, float other) {
+        own = no_own ? 0.f : own;
+        other = no_sib ? 0.f : other;
         return i & 1 ? __builtin_fmaf(ws, other, wo * own) : __builtin_fmaf(wo, own, ws * other);
       };
       l_tot[0] = merged(l_tot[0], ls);

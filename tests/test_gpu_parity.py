@@ -256,6 +256,36 @@ def test_split_rows_many_chunks(n, block):
         PR.compare_attention(to_f64(runs[0][h]), to_f64(o_fixed[h]), rows=rows, where=f"many chunks n{n} h{h} vs fixed")
 
 
+def test_split_rows_chunk_without_keys():
+    """A chunk of a split row that holds only entries outside [0, qb] takes no part in the
+    merge, whatever the block read in their place holds: key block 0, which these rows do not
+    list, has infinite and NaN values, and the rows stay the attention over their own blocks.
+    Chunks of eight entries without a key first, last, in the middle and as both of a pair; a
+    row of them alone is 0."""
+    C = _crisp()
+    _say("split rows, chunks without keys")
+    n, block, hq = 4096, 128, 2
+    nb = n // block
+    junk, lo, hi = [-5] * 8, list(range(1, 9)), list(range(9, 17))
+    long_rows = {31: lo + junk + hi, 30: junk + junk + lo + hi, 29: lo + junk, 28: junk + lo, 27: lo + hi + junk, 26: junk + junk}
+    rows = [long_rows.get(qb, [qb]) for qb in range(nb)]
+    sets = [sorted({x for x in r if x >= 0}) for r in rows]
+    rp, ci = _csr_from_rows(rows, nb)
+    rp, ci = np.repeat(rp, hq, axis=0), np.repeat(ci, hq, axis=0)
+    q, k, v = _rand(hq, n, seed=41), _rand(1, n, seed=42), _rand(1, n, seed=43)
+    K, V = to_f64(k)[0], to_f64(v)[0]
+    v[0, :block:2] = math.inf
+    v[0, 1:block:2] = math.nan
+    args = (q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(rp).to(DEV), torch.from_numpy(ci).to(DEV), block)
+    o = C.crisp_sparse_attn(*args)
+    torch.cuda.synchronize()
+    idx = PR.qb_rows([27, 28, 29, 30, 31], block, n)
+    assert (to_f64(o)[:, 26 * block:27 * block] == 0).all()
+    for h in range(hq):
+        ref = O.sparse_attention(to_f64(q)[h], K, V, sets, block, 1 / math.sqrt(128), qbs=[27, 28, 29, 30, 31])
+        PR.compare_attention(to_f64(o[h]), ref, rows=idx, where=f"chunks without keys h{h}")
+
+
 def test_more_than_2p21_units():
     """A layer with more (head, query block) units than a split work item can name
     (2^21): 65 query heads over one KV head at the longest length with B = 64 (2,129,920
