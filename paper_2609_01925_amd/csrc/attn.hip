@@ -321,6 +321,79 @@ __device__ __forceinline__ void pv_tile(int vbuf, const Offsets& off, const bf16
     }
 }
 
+// The softmax half of a step beside the PV product of the tile before: pn = exp2(s c - mc) and
+// o += V^T pp, the lane's sum of pn returned (sum_tile's, in its order).  The first kPre pairs of
+// probabilities come ahead of the MFMAs, then one pair passes under each MFMA and the row
+// sums under the last ones; V operands are read kAhead MFMAs ahead, and a pair is packed one MFMA after
+// its exponentials (no wait states).  The order is fixed here, MFMA by MFMA: left to the
+// scheduler it changed with code elsewhere in the kernel, and with it how far the workgroups
+// that share K/V tiles drift apart, so how often a tile is still in L2.  HBM reads of the
+// attention with the order that came with the merge after the loop -> this one (with the order
+// before the merge): 512k tokens, 7 heads 360 -> 137 GB (219) on one card, 361 -> 207 GB (252)
+// on another; 128k, 32 heads 30.2 -> 17.0 GB (17.0).  Whole prefill there: 209.0 -> 204.8 ms
+// (207.2) and 198.7 -> 196.3 (197.0), 512k with 28 heads 586.2 -> 578.1 (582.9); 128k 44.32 ->
+// 44.49 (44.48) and 42.36 -> 42.44 (42.47); 32k, 64-row blocks 4.06 -> 4.04 (4.07).  Other pairs
+// ahead / MFMAs ahead, where this one takes 204.8 and 44.5: 2 / 2 206.9 ms at 512k and 44.8 at
+// 128k, 1 / 2 207.8 and 45.0, 3 / 1 210.1 and 45.6, 4 / 2 and 4 / 3 205.1 and 44.6.
+template <int NMB>
+__device__ __forceinline__ float exp_pv_tile(const f32x16 (&s)[NMB], float c, float mc, bf16x8 (&pn)[NMB][2], int vbuf,
+                                             const Offsets& off, const bf16x8 (&pp)[NMB][2], f32x16 (&o)[4]) {
+  constexpr int M = 8 * NMB;  // MFMAs, and pairs of probabilities
+  constexpr int kPre = 3, kAhead = 2;
+  float e0[M], e1[M], part[2] = {0.f, 0.f};
+  auto expo = [&](int p) {
+    const int mb = p >> 3, i = 2 * (p & 7);
+    e0[p] = fast_exp2(__builtin_fmaf(s[mb][i], c, -mc));
+    e1[p] = fast_exp2(__builtin_fmaf(s[mb][i + 1], c, -mc));
+    asm volatile("" : "+v"(e0[p]), "+v"(e1[p]));  // formed here (so pack and dot)
+  };
+  auto pack = [&](int p) {
+    uint32_t u = __builtin_bit_cast(uint32_t, pack_bf16(e0[p], e1[p]));
+    asm volatile("" : "+v"(u));
+    const bf16x2 pr = __builtin_bit_cast(bf16x2, u);
+    pn[p >> 3][(p >> 2) & 1][2 * (p & 3)] = pr[0];
+    pn[p >> 3][(p >> 2) & 1][2 * (p & 3) + 1] = pr[1];
+  };
+  auto dot = [&](int i) {  // the two partial sums in turn (a chain's next step waits for the last)
+    const int mb = i >> 3, hh = i & 1, e = 2 * ((i >> 1) & 3);
+    bf16x2 pr;
+    pr[0] = pn[mb][hh][e];
+    pr[1] = pn[mb][hh][e + 1];
+    part[hh] = dot2_bf16_sum(pr, part[hh]);
+    asm volatile("" : "+v"(part[hh]));
+  };
+  bf16x8 av[M];
+  auto load = [&](int x) {
+    const int vb = vbuf + (32 * (x >> 3) + 16 * ((x >> 2) & 1)) * 256, db = x & 3;
+    av[x] = cat(lds_ld_tr(vb + off.v[db][0]), lds_ld_tr(vb + off.v[db][1]));
+  };
+#pragma unroll
+  for (int x = 0; x < kAhead; ++x) load(x);
+#pragma unroll
+  for (int p = 0; p < kPre; ++p) {
+    expo(p);
+    if (p > 0) pack(p - 1);
+  }
+  constexpr int kBeside = M - kPre;  // pairs beside MFMAs
+#pragma unroll
+  for (int x = 0; x < M; ++x) {
+    __builtin_amdgcn_sched_barrier(0);
+    o[x & 3] = mfma32(av[x], pp[x >> 3][(x >> 2) & 1], o[x & 3]);
+    if (x + kAhead < M) load(x + kAhead);
+    if (x < kBeside) {
+      pack(kPre + x - 1);
+      expo(kPre + x);
+    } else {
+      if (x == kBeside) pack(M - 1);
+#pragma unroll
+      for (int i = 0; i < M; ++i)
+        if (i * kPre / M == x - kBeside) dot(i);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  return part[0] + part[1];
+}
+
 // Partial results of split rows are exchanged between workgroups of one launch, which may
 // run on XCDs with L2 caches of their own: their loads and stores carry sc1 (agent scope),
 // so a store has reached the level that all XCDs share once its wave has waited for it,
@@ -485,12 +558,16 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, i
 #pragma unroll
       for (int h = 0; h < QH; ++h) {
         const float mc = m_run[h] == -__builtin_inff() ? 0.f : m_run[h] * a.c;
+        if constexpr (!DENSE && !decltype(first)::value) {
+          ts[h] = exp_pv_tile<NMB>(s[h], a.c, mc, pn[h], vst(1 - P), off, pp[h], o[h]);
+        } else {
 #pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) exp_sub(s[h][mb], a.c, mc, pn[h][mb]);
-        ts[h] = sum_tile<NMB>(pn[h]);
+          for (int mb = 0; mb < NMB; ++mb) exp_sub(s[h][mb], a.c, mc, pn[h][mb]);
+          ts[h] = sum_tile<NMB>(pn[h]);
+        }
         grow = grow || !(ts[h] <= kSumLimit) || m_run[h] == -__builtin_inff();
       }
-      if (!decltype(first)::value) pv_tile<QH, NMB>(vst(1 - P), off, pp, o);
+      if (DENSE && !decltype(first)::value) pv_tile<QH, NMB>(vst(1 - P), off, pp, o);
       race_sync();
       // Keeps the probabilities formed here, beside the PV product, rather than
       // letting the compiler sink them into the no-rescale path.
