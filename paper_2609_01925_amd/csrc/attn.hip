@@ -47,7 +47,8 @@
 // ones fill the CUs as they free up, with no loop, queue or split rows around each unit
 // (2k-4k layers of 32 heads 11-12% faster than the persistent grid with split rows, 8k
 // 3-10% faster, 16k 14% slower).  With fewer units (few heads) the persistent grid takes
-// items i, i + grid, ... of that list and splits long rows.
+// items i, i + grid, ... of that list and splits long rows; so does a longer layer with units
+// for at most half of that grid, whose pops would meet on one counter.
 #include <atomic>
 #include <type_traits>
 
@@ -71,7 +72,7 @@ struct Tile {
 constexpr float kSumLimit = 256.0f;          // a lane's tile sum of P above this forces a rescale
 constexpr int kCostBuckets = 8192;
 constexpr int kOneShotMinLen = 1 << 19;  // from this length on, sparse lists run one unit per workgroup
-constexpr int kStaticListMaxLen = 8192;  // up to this length too, from one list by workgroup index (no atomics)
+constexpr int kStaticListMaxLen = 8192;  // up to this length (and with few units) items come from one list by workgroup index
 // Shortest chunk of a split row, in list entries: shorter ones cost more in partial results
 // (66 KB each way) than the shorter critical path saves (attention at 4k tokens, 8 heads:
 // 56 us, at 6 entries 65 us; 2k tokens, 8 heads: 37.6 and 39.3 us).
@@ -1160,7 +1161,14 @@ hipError_t launch_attn(const Dims& d, float scale, const uint16_t* q, const uint
     const size_t units = (size_t)d.hq * d.nb;
     const bool short_one = d.n <= kStaticListMaxLen && units >= (size_t)pg;
     a.one_shot = d.n >= kOneShotMinLen || short_one ? 1 : 0;
-    a.static_list = d.n <= kStaticListMaxLen ? 1 : 0;
+    // Few units, too: where the grid has twice as many workgroups as units, most of them find
+    // no second item (many not a first), and their pops only queue up on one counter, ahead of those
+    // that do.  Attention (one launch with its list builder), queues -> one list: 24k tokens, 1
+    // head (192 units) 66.5 -> 49.2 us; 12k, 2 heads 96.1 -> 72.6; 32k, 1 head (256, the limit)
+    // 75.1 -> 64.1; 64-row blocks (limit 512 units): 16k, 1 head 75.1 -> 56.0, 16k, 2 heads
+    // 140.6 -> 120.5.  Above: 24k, 2 heads (384 of 512) 153 -> 151 and 187 -> 196, 32k, 2 heads
+    // (512) 216 -> 224 and 282 -> 291, as the groups' tiles then spread over every XCD.
+    a.static_list = d.n <= kStaticListMaxLen || units <= (size_t)pg / 2 ? 1 : 0;
     a.split_slots = short_one ? 0 : sl.slots;  // the slots stay reserved, unused
     if (a.split_slots > 0) {
       a.slot_base = reinterpret_cast<int*>(sc + sl.slot_base);

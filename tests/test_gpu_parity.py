@@ -159,11 +159,13 @@ def _csr_from_rows(rows, nb):
     return rp, ci
 
 
-@pytest.mark.parametrize("case", ["full-b128", "full-b128-8k", "full-b64-ragged", "junk-first-chunk"])
+@pytest.mark.parametrize("case", ["full-b128", "full-b128-queues", "full-b128-8k", "full-b64-ragged",
+                                  "full-b64-queues", "junk-first-chunk"])
 def test_split_rows(case):
     """Rows far longer than the layer's work per workgroup are split into chunks whose
-    partial results are merged (online-softmax merge of (O, m, l) in chunk order).  Few heads
-    with full causal lists force it (on the persistent grid); the merged rows match the
+    partial results are merged (online-softmax merge of (O, m, l) in a fixed pairwise tree).
+    Few heads with full causal lists force it (on the persistent grid, from one list or, with
+    units for more than half of it, from the groups' queues); the merged rows match the
     oracle, runs are bitwise repeatable, and the split rows round differently
     from the unsplit fixed-order launch (which shows the split path ran).  junk-first-chunk:
     a row's first chunk holds only invalid entries (m = -inf, weighing nothing in the
@@ -191,8 +193,9 @@ def test_split_rows(case):
     else:
         # 8k: a short layer (units from one list in a fixed stride) with too few units for
         # one workgroup each
-        n, block, hq = {"full-b128": (16384, 128, 1), "full-b128-8k": (8192, 128, 1),
-                        "full-b64-ragged": (16000, 64, 2)}[case]
+        n, block, hq = {"full-b128": (16384, 128, 1), "full-b128-queues": (16384, 128, 3),
+                        "full-b128-8k": (8192, 128, 1), "full-b64-ragged": (16000, 64, 2),
+                        "full-b64-queues": (16000, 64, 3)}[case]
         nb = O.n_blocks(n, block)
         sets = O.dense_causal_sets(nb)
         rp = np.zeros((hq, nb + 1), np.int32)
@@ -284,6 +287,32 @@ def test_split_rows_chunk_without_keys():
     for h in range(hq):
         ref = O.sparse_attention(to_f64(q)[h], K, V, sets, block, 1 / math.sqrt(128), qbs=[27, 28, 29, 30, 31])
         PR.compare_attention(to_f64(o[h]), ref, rows=idx, where=f"chunks without keys h{h}")
+
+
+@pytest.mark.parametrize("n,hq,block,queues", [(24576, 1, 128, False), (32768, 1, 128, False), (32769, 1, 128, True),
+                                               (16384, 2, 64, False), (16385, 2, 64, True)])
+def test_few_units_take_no_queue(n, hq, block, queues):
+    """Layers with units for at most half of the persistent grid take their items from one
+    list by workgroup index: no workgroup pops a queue (the schedule area starts with the
+    queues' counters).  One unit more and they pop.  Rows against float64 attention."""
+    C = _crisp()
+    _say(f"few units n={n} hq={hq} B={block}")
+    nb = O.n_blocks(n, block)
+    sets = [sorted({0, qb} | {round(x) for x in np.linspace(0, qb, 12)}) for qb in range(nb)]
+    rp, ci = _csr_from_rows(sets, nb)
+    rp, ci = np.repeat(rp, hq, axis=0), np.repeat(ci, hq, axis=0)
+    q, k, v = _rand(hq, n, seed=51), _rand(1, n, seed=52), _rand(1, n, seed=53)
+    args = (q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(rp).to(DEV), torch.from_numpy(ci).to(DEV), block)
+    ws = torch.empty(C.crisp_sparse_workspace_size(C.shape_of(q, k, block)), dtype=torch.uint8, device=DEV)
+    o = C.crisp_sparse_attn(*args, ws=ws)
+    torch.cuda.synchronize()
+    pops = ws[:32].view(torch.int32).cpu()
+    assert bool((pops > 0).any()) == queues, pops.tolist()
+    qbs = [0, 1, nb // 2, nb - 1]
+    idx = PR.qb_rows(qbs, block, n)
+    for h in range(hq):
+        ref = O.sparse_attention(to_f64(q)[h], to_f64(k)[0], to_f64(v)[0], sets, block, 1 / math.sqrt(128), qbs=qbs)
+        PR.compare_attention(to_f64(o[h]), ref, rows=idx, where=f"few units n{n} h{h}")
 
 
 def test_more_than_2p21_units():
