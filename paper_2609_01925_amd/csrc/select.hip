@@ -980,6 +980,30 @@ __device__ void radix_head(const SelArgs& a, const float* At, unsigned long long
   }
 }
 
+// Which of the key blocks base + 64 x + lane, x = 0..3, row qb of a VS head lists (vm, sm: the
+// head's direction masks).  Like the scores of a PE row below, the masks are read whole and
+// unconditionally (a block past the diagonal is clamped to it), so that the reads of all four
+// chunks are in flight together: behind a test each is a branch of its own and waits for the
+// one before.  crisp_route_select in a graph, with a test / unconditional (the separate launches
+// that sel_mid replaced), one head: 256 blocks, VS 30.4 / 24.4 us (27.1), PE 67.5 / 65.4 (62.2); 200
+// blocks, VS 23.3 / 20.1 (17.0), PE 50.6 / 49.3 (52.9).  Launched one by one, as in a stream, those
+// launches take 49 us or more for VS at 256 blocks and sel_mid's 31.
+__device__ __forceinline__ void vs_row_chunks(int nb, int qb, int base, const uint8_t* vm, const uint8_t* sm, bool (&sel)[4]) {
+  const int l = threadIdx.x & 63;
+  uint8_t v[4], s[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int kb = base + 64 * x + l, kc = kb < qb ? kb : qb;
+    v[x] = vm[kc];
+    s[x] = sm[nb - 1 - qb + kc];
+  }
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int kb = base + 64 * x + l;
+    sel[x] = (kb <= qb) & ((kb == 0) | (kb == qb) | ((v[x] | s[x]) != 0));
+  }
+}
+
 // Per-row counts of row qb, by one wave.  VS (vm, sm: the head's direction masks): x = row
 // size.  PE (row: its scores): x = #(> t*), y = #(== t*), z = flags (1: block 0 > t*, 2:
 // block 0 == t*, 4: block qb > t*, 8: block qb == t*).
@@ -990,11 +1014,7 @@ __device__ __forceinline__ int4 csr_count_row(bool vs, int nb, int qb, const uin
     int cnt = 0;
     for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
       bool sel[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const int kb = base + 64 * x + l;
-        sel[x] = kb <= qb && (kb == 0 || kb == qb || vm[kb] || sm[nb - 1 - qb + kb]);
-      }
+      vs_row_chunks(nb, qb, base, vm, sm, sel);
 #pragma unroll
       for (int x = 0; x < 4; ++x) cnt += __popcll(__ballot(sel[x]));
     }
@@ -1006,7 +1026,7 @@ __device__ __forceinline__ int4 csr_count_row(bool vs, int nb, int qb, const uin
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int kb = base + 64 * x + l;
-      bv[x] = kb <= qb ? fbits(row[kb]) : 0u;
+      bv[x] = fbits(row[kb < qb ? kb : qb]);
     }
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
@@ -1107,11 +1127,7 @@ __device__ __forceinline__ void csr_fill_row(bool vs, int nb, int qb, const uint
   if (vs) {
     for (int base = 0; base <= qb; base += 256) {  // four 64-entry chunks, their loads issued together
       bool sv[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const int kb = base + 64 * x + l;
-        sv[x] = kb <= qb && (kb == 0 || kb == qb || vm[kb] || sm[nb - 1 - qb + kb]);
-      }
+      vs_row_chunks(nb, qb, base, vm, sm, sv);
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         const int kb = base + 64 * x + l;
@@ -1128,7 +1144,7 @@ __device__ __forceinline__ void csr_fill_row(bool vs, int nb, int qb, const uint
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int kb = base + 64 * x + l;
-      bv[x] = kb <= qb ? fbits(row[kb]) : 0u;
+      bv[x] = fbits(row[kb < qb ? kb : qb]);
     }
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
