@@ -73,6 +73,7 @@ constexpr float kSumLimit = 256.0f;          // a lane's tile sum of P above thi
 constexpr int kCostBuckets = 8192;
 constexpr int kOneShotMinLen = 1 << 19;  // from this length on, sparse lists run one unit per workgroup
 constexpr int kStaticListMaxLen = 8192;  // up to this length (and with few units) items come from one list by workgroup index
+constexpr int kOneGroupListMaxLen = 16384;  // up to this length layers of one KV group do so with more units
 // Shortest chunk of a split row, in list entries: shorter ones cost more in partial results
 // (66 KB each way) than the shorter critical path saves (attention at 4k tokens, 8 heads:
 // 56 us, at 6 entries 65 us; 2k tokens, 8 heads: 37.6 and 39.3 us).
@@ -773,6 +774,11 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
   int* s_unit = reinterpret_cast<int*>(smem + 2 * Tile<BQ>::kRing);
   const int x0 = home_queue(a, blockIdx.x % kNumXcd);
   const int* start = a.counter + 8;
+  // Workgroups past the number of items leave at once (a layer with fewer units than the grid,
+  // no row split): popping, they would take items from those before them, and the dispatcher has
+  // filled some CUs with four workgroups where three each have an item (window lists with 768 units in 64-row
+  // blocks: 24k tokens, 2 heads 98 -> 88 us, 64 blocks wide 151 -> 135).
+  if (!a.static_list && (int)blockIdx.x >= start[kNumXcd]) return;
   // Queues this workgroup has seen run dry (thread 0): they are never tried again.
   // A queue whose counter already reads past its end is skipped without an atomic
   // (a stale read only costs an extra atomic: counters never decrease).
@@ -844,14 +850,24 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
 // rows longer than C = max(ceil(T / G'), 8, ceil(N_b / 1024)) are cut into
 // ceil(L / C) chunks, each a work item of its own that leaves a partial result
 // in a slot or merges its sibling's (attn_unit).  Chunks number at most
-// T / C + (rows longer than C) <= 2 G' <= slots.  When that bound on the slots and not
-// the grid sets C (few units), 5/4 of the grid's ceil(T / grid) is tried first and taken if
-// its chunks fit the slots (whole prefill, us, C from 1x / 5/4 / 3/2 of it / the bound
-// alone: 24k tokens, 8 heads, 64-row blocks 671 / 690 / 751 / 761; 12k, 16 heads, structured
-// heads 407 / 387 / 386 / 386: at 1x nearly every long row is split).  The decision depends
-// only on the lists and the grid, so results do not depend on timing.
+// T / C + (rows longer than C) <= 2 G' <= slots.
+// 1. Where the slots and not the grid set that C, it is more than 5/4 of the grid's share
+//    T / grid (64-row blocks, whose grid is twice the slots' 512 rows; few units): C from 4/5 of
+//    the grid in place of G' is then tried first and taken if its chunks, which the bound above
+//    does not cover, fit the slots by count.  Whole prefill, us, C from 1x / 5/4 / 3/2 of the share / the
+//    slots' bound alone, 64-row blocks: 24k tokens, 8 heads 671 / 690 / 751 / 761; 12k, 16 heads,
+//    structured 407 / 387 / 386 / 386 (at 1x nearly every long row is split).
+// 2. Where the grid sets C (128-row blocks from 512 units on) it stays at 1x.  1x / 5/4 there: 32k
+//    tokens, 2 heads 370 / 404 and 328 / 347 (structured), 20k, 4 heads 281 / 294 and 221 / 216, 16k,
+//    8 heads 300 / 310 and 248 / 232, 12k, 16 heads 348 / 345 and 281 / 274; 64k and 128k alike.
+// 3. A row is split for the time of the longest: not at all unless that one has kMinChunk entries
+//    more than C, and at 5/4 of the grid's share not unless it has 2 kMinChunk more.  A window list's
+//    rows all have about the share, and a split then only adds partial results: attention over
+//    lists of up to 29 to 41 blocks, always split / by this rule: 12k, 4 heads, 64-row blocks 64.4 /
+//    58.5, 24k, 2 heads, 64-row blocks 102.6 / 90.0; 10k, 6 heads 114.7 / 90.0.
+// The decision depends only on the lists and the grid, so results do not depend on timing.
 //
-// One workgroup builds everything and resets the queue and arrival counters; the order
+// attn_schedule is one workgroup that builds everything and resets the queue and arrival counters; the order
 // within one length is arbitrary (it only decides which workgroup runs an item,
 // never a result).  Schedule area: int counters[8], int start[9], int C (at 17,
 // INT_MAX when no row is split); items from int offset 64; then slot_base[units],
@@ -957,7 +973,7 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
     gp = gp < 1 ? 1 : gp;
     long long c = chunk_for(gp);
     const int cg = (int)chunk_for((long long)a.grid * 4 / 5);
-    if (cg < c && s_max > cg) {
+    if (cg < c && s_max - cg >= 2 * kMinChunk) {
       int chunks = 0;
       each_unit([&](int, int L) { chunks += L > cg ? (L + cg - 1) / cg : 0; });
       chunks = wave_sum_i(chunks);
@@ -965,7 +981,7 @@ __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
       __syncthreads();
       if (s_fit <= a.split_slots) c = cg;
     }
-    if (s_max > c) C = (int)c;
+    if (s_max - c >= kMinChunk) C = (int)c;
   }
   auto key = [&](int h, int len) {
     return (a.static_list ? 0 : unit_queue(a, h)) * kQueueBuckets + (kQueueBuckets - 1 - cost_bucket(len));
@@ -1167,17 +1183,32 @@ hipError_t launch_attn(const Dims& d, float scale, const uint16_t* q, const uint
     // head (192 units) 66.5 -> 49.2 us; 12k, 2 heads 96.1 -> 72.6; 32k, 1 head (256, the limit)
     // 75.1 -> 64.1; 64-row blocks (limit 512 units): 16k, 1 head 75.1 -> 56.0, 16k, 2 heads
     // 140.6 -> 120.5.  Above: 24k, 2 heads (384 of 512) 153 -> 151 and 187 -> 196, 32k, 2 heads
-    // (512) 216 -> 224 and 282 -> 291, as the groups' tiles then spread over every XCD.
-    a.static_list = d.n <= kStaticListMaxLen || units <= (size_t)pg / 2 ? 1 : 0;
+    // (512) 216 -> 224 and 282 -> 291, as the groups' tiles then spread over every XCD.  One KV
+    // group is on every XCD anyhow and its workgroups all pop one counter, so it takes the
+    // list further, while its K and V fit the L2s in part (up to 16k tokens, 8 MB; a 64-block-wide
+    // window at 48k, 1 head, 64-row blocks 161 -> 237) and, with 128-row blocks, up to 5/8 of the grid
+    // (queues -> list, attention: 8320, 4 heads (260) 73 -> 61; 12k, 3 heads (288) 94 -> 83; 40k, 1 head,
+    // 64-wide window 187 -> 211; 12k, 4 heads (384), full lists 178 -> 181; 16k, 4 heads (512), full
+    // lists 273 -> 308; 64-row blocks: 8320, 4 heads (520) 102 -> 85; 12k, 4 heads (768) 148 -> 132;
+    // 16k, 4 heads (1024) 212 -> 195).
+    const size_t one_group = d.hkv == 1 && d.n <= kOneGroupListMaxLen ? (size_t)pg * (d.B == 128 ? 5 : 8) / 8 : 0;
+    a.static_list = d.n <= kStaticListMaxLen || units <= (size_t)pg / 2 || units <= one_group ? 1 : 0;
     a.split_slots = short_one ? 0 : sl.slots;  // the slots stay reserved, unused
     if (a.split_slots > 0) {
       a.slot_base = reinterpret_cast<int*>(sc + sl.slot_base);
       a.arrived = reinterpret_cast<int*>(sc + sl.arrived);
       a.parts = reinterpret_cast<float*>(sc + sl.parts);
     }
-    // items: the units, and at most one less than the slots more where rows are split
+    // items: the units, and at most one less than the slots more where rows are split.  With 128-row
+    // blocks queues get no more workgroups than units: rows are cut at the mean there, so the
+    // chunks are few and short, and what a workgroup per item gains is less than two on every CU
+    // cost (attention, a workgroup per item / per unit: 24k tokens, 2 heads in 2 groups 197 / 185 us, 40k, 1 head
+    // 107 / 104; 10k, 4 heads in 4 groups 109 / 113).  64-row blocks, whose grid is twice the slots' rows:
+    // 24k, 2 heads in 2 groups 226 / 237, 40k, 1 head 182 / 206, 9000, 4 heads in 4 groups 116 / 128;
+    // 16k, 3 heads in 3 groups 116 / 106).
     const size_t items = units + (a.split_slots > 0 ? (size_t)a.split_slots - 1 : 0);
-    grid = (int)(a.one_shot || items < (size_t)pg ? items : (size_t)pg);
+    const size_t most = a.static_list || d.B == 64 || units > (size_t)pg ? (size_t)pg : units;
+    grid = (int)(a.one_shot || items < most ? items : most);
     a.grid = grid < pg ? grid : pg;
     hipLaunchKernelGGL(attn_schedule, dim3(1), dim3(1024), 0, stream, a);
     const hipError_t e = hipGetLastError();

@@ -290,11 +290,15 @@ def test_split_rows_chunk_without_keys():
 
 
 @pytest.mark.parametrize("n,hq,block,queues", [(24576, 1, 128, False), (32768, 1, 128, False), (32769, 1, 128, True),
-                                               (16384, 2, 64, False), (16385, 2, 64, True)])
+                                               (16384, 2, 64, False), (16385, 2, 64, True),
+                                               (8320, 4, 128, False), (10240, 4, 128, False), (10241, 4, 128, True),
+                                               (16384, 4, 64, False), (16385, 3, 64, True)])
 def test_few_units_take_no_queue(n, hq, block, queues):
     """Layers with units for at most half of the persistent grid take their items from one
     list by workgroup index: no workgroup pops a queue (the schedule area starts with the
-    queues' counters).  One unit more and they pop.  Rows against float64 attention."""
+    queues' counters).  So do layers of one KV group up to 16384 tokens with units for 5/8 of it (128-row
+    blocks) or all of it (64-row blocks).  One unit or token more and they pop.  Rows against
+    float64 attention."""
     C = _crisp()
     _say(f"few units n={n} hq={hq} B={block}")
     nb = O.n_blocks(n, block)
@@ -313,6 +317,24 @@ def test_few_units_take_no_queue(n, hq, block, queues):
     for h in range(hq):
         ref = O.sparse_attention(to_f64(q)[h], to_f64(k)[0], to_f64(v)[0], sets, block, 1 / math.sqrt(128), qbs=qbs)
         PR.compare_attention(to_f64(o[h]), ref, rows=idx, where=f"few units n{n} h{h}")
+
+
+@pytest.mark.parametrize("n,hq,hkv,block", [(24576, 2, 2, 64), (12288, 4, 1, 64), (10240, 6, 2, 128), (16384, 3, 3, 64)])
+def test_rows_of_about_the_share_stay_whole(n, hq, hkv, block):
+    """A caller's window lists, whose longest rows hold only a few entries more than the layer's
+    work per workgroup: a split would save less than its partial results cost, so no row is
+    split and the output is the fixed-order launch's bit for bit."""
+    C = _crisp()
+    _say(f"window lists n={n} {hq}/{hkv} B={block}")
+    nb = O.n_blocks(n, block)
+    sets = [[j for j in range(qb + 1) if j == 0 or qb - j < 16 or j % 16 == 8] for qb in range(nb)]
+    rp, ci = _csr_from_rows(sets, nb)
+    rp, ci = np.repeat(rp, hq, axis=0), np.repeat(ci, hq, axis=0)
+    q, k, v = _rand(hq, n, seed=61), _rand(hkv, n, seed=62), _rand(hkv, n, seed=63)
+    args = (q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(rp).to(DEV), torch.from_numpy(ci).to(DEV), block)
+    o, o_fixed = C.crisp_sparse_attn(*args), C.crisp_sparse_attn(*args, balance=False)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o_fixed)
 
 
 def test_more_than_2p21_units():
