@@ -418,8 +418,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(const AttnArgs& a, 
 // workgroup ever waits for another.  A merge kernel after this one, which the host (not
 // knowing whether a row is split) launched for every layer, took 4.6 us without and 7.2 us
 // with split rows, and its cost had kept chunks long: attention at 4k tokens and 2 heads
-// 58.7 -> 46.0 us, at 24k tokens, 8 heads and 64-row blocks 703 -> 583 us (one workgroup
-// merging all chunks of a row in turn: 50 and 612 us).
+// 58.7 -> 46.0 us, at 24k tokens, 8 heads, 64-row blocks and the lists of a layer with 40 % diffuse heads
+// 675 -> 617 us (all chunks of a row merged by one workgroup in turn, at 4k: 50 us).
 template <int BQ, bool DENSE>
 __device__ __forceinline__ void attn_unit(const AttnArgs& a, int head, int qb, int lds0, const Offsets& off,
                                           const Fetch<Geo<BQ>::kWaves>& fe, int tid, int* slots = nullptr) {
@@ -901,9 +901,11 @@ __device__ __forceinline__ void for_units(const AttnArgs& a, int total, int tid,
   }
 }
 
-// It is one workgroup and runs once, so latency and instruction fetch bound it, not work:
-// the row lengths are read once (in batches of eight loads) and kept in LDS, and the passes
-// are short rolled loops over them.  Kernel time with lengths re-read from memory or held
+// The work-list builder.  It is one workgroup and runs once, so latency and instruction fetch bound it,
+// not work: up to kLenCache units the row lengths are read once (in batches of eight loads) and kept in
+// LDS, and the passes are rolled loops over them.  Larger layers read them again in each pass, by
+// for_units, which stands unrolled in every pass beside the loop and makes up most of the kernel's code
+// (128k tokens, 32 heads 66 us and 512k, 28 heads 180 us either way, of 43 and 600 ms).  Kernel time with lengths re-read from memory or held
 // in registers by unrolled passes -> now: 20k tokens, 32 heads 15.6 -> 12.6 us; 32k, 64-row
 // blocks 31.6 -> 27.3; 8k 8.5 -> 7.4; 2k 5.9 -> 4.6.  (All passes unrolled over registers
 // with the atomics of equal keys combined per wave: 22.8, 42, 9.0 and 8.3 us.)

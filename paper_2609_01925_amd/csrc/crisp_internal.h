@@ -67,9 +67,13 @@ constexpr int kFoldBlocks = 256;
 // Up to this many query rows (heads x tokens) the pooling runs beside the estimator's pass,
 // for every head (the routes are not known yet), and up to kSmallSelectBlocks blocks the
 // combine inside the selection.  That saves one or two launches for the pooling of the VS
-// heads' Q, which passes under the pass while Q is small.  Whole prefill without -> with: 4k
-// tokens, 2 heads 72.2 -> 67.1 us; 32 heads at 2k 70.5 -> 65.0, 4k 116.4 -> 111.8, 8k (the
-// limit) 256.2 -> 249.7; 28 heads at 5k, 64-row blocks 191.1 -> 187.0.
+// heads' Q, which passes under the pass while Q is small or in the caches.  Whole prefill, apart / beside, us,
+// inputs in the caches; and after 1 GiB of other writes: 4k tokens, 2 heads 73.1 / 67.3; 88.2 / 77.5.
+// 32 heads: 2k 75.2 / 70.0; 89.5 / 81.0, 4k 117.5 / 112.9; 131.0 / 125.8, 8k (the limit) 316.1 / 310.9; 329.2 /
+// 329.4.  16k, 16 heads (the limit) 522.0 / 519.5; 533.1 / 538.1.  Above it the launches saved no longer
+// outweigh the reads of Q from HBM: 10k, 32 heads 515.8 / 512.0; 529.4 / 535.7, 16k, 32 heads 1036.6 /
+// 1037.2; 1053.0 / 1064.3, 32k, 16 heads 1168.1 / 1167.5; 1191.0 / 1202.2.  The first pass of a fresh layer with
+// its new buffers, by the host's clock: 2k 116.1 / 111.5, 8k 300.6 / 299.9.
 constexpr int64_t kPoolBesideRows = 262144;
 
 // route_score is C_struct (tau = tau_proxy) or D_JS (tau = tau_jsd); vs_mode 0 is the
