@@ -226,18 +226,21 @@ def test_split_rows(case):
 def test_split_rows_many_chunks(n, block):
     """Rows split into 2 to 16 chunks (8 entries each: every other row lists two blocks), odd
     counts among them, so that the pairwise merge passes chunks without a sibling up the
-    tree: against float64 attention, bitwise repeatable, and within the attention tolerance
-    of the unsplit fixed-order launch."""
+    tree, and the full tree of four levels: against float64 attention, bitwise repeatable, and
+    within the attention tolerance of the unsplit fixed-order launch, from which every split row
+    and no other differs in some bit."""
     C = _crisp()
     _say(f"split rows, many chunks: n={n} B={block}")
     nb = O.n_blocks(n, block)
     hq = 2
-    lengths = [9, 16, 17, 25, 33, 40, 41, 56, 64, 65, 72, 89, 104, 113, 120]
-    long_rows = {nb - 1 - i: ln for i, ln in enumerate(lengths) if ln <= nb - i}
+    lengths = [125, 113, 104, 89, 72, 65, 64, 56, 41, 40, 33, 25, 17, 16, 9]  # 16, 15, 13, 12, ... 2 chunks
+    long_rows = {nb - 1 - i: ln for i, ln in enumerate(lengths)}
+    assert all(ln <= qb + 1 for qb, ln in long_rows.items())
     sets = []
     for qb in range(nb):
         ln = long_rows.get(qb)
         sets.append(sorted({0, qb}) if ln is None else sorted({round(x) for x in np.linspace(0, qb, ln)}))
+        assert ln is None or len(sets[-1]) == ln
     flat = np.concatenate([np.asarray(r, np.int32) for r in sets])
     rp = np.zeros((hq, nb + 1), np.int32)
     rp[:, 1:] = np.cumsum([len(r) for r in sets])
@@ -252,7 +255,10 @@ def test_split_rows_many_chunks(n, block):
     Q, K, V = to_f64(q), to_f64(k)[0], to_f64(v)[0]
     qbs = sorted(long_rows) + [0, nb // 2]
     rows = PR.qb_rows(sorted(qbs), block, n)
-    assert not torch.equal(runs[0][:, rows], o_fixed[:, rows]), "no row was split"
+    for h in range(hq):
+        for qb in range(nb):
+            at = slice(qb * block, min((qb + 1) * block, n))
+            assert torch.equal(runs[0][h, at], o_fixed[h, at]) == (qb not in long_rows), f"h{h} qb{qb} split?"
     for h in range(hq):
         ref = O.sparse_attention(Q[h], K, V, sets, block, 1 / math.sqrt(128), qbs=sorted(qbs))
         PR.compare_attention(to_f64(runs[0][h]), ref, rows=rows, where=f"many chunks n{n} h{h}")
@@ -970,20 +976,28 @@ def test_flexprefill_prefill_matches_stagewise():
 
 
 def _stagewise_cases():
-    # (name, layer, parameters); up to 64 blocks prefill's selection forms p_v and p_s from
-    # the estimator's sums itself, past that it reads the estimator's own p_v and p_s
+    # (name, layer, parameters); up to 256 blocks prefill's selection forms p_v and p_s from the
+    # estimator's sums itself, past that it reads the estimator's own p_v and p_s; up to
+    # 262144 query rows the estimator's launch pools Q and K, and up to 64 blocks the selection
+    # then forms C_struct, too.  The last five: 64 blocks above the rows, 65 and 128 above them,
+    # 128 at exactly that many, 258 blocks.
     return [("5000 4/1", lambda: custom_config(5000, 4, 1, block=128, config_id=140), {}),
             ("pe8k 32/8 nb64", lambda: structured_pe_config(8192), {}),
             ("4000 8/2 B64 median kmin3", lambda: custom_config(4000, 8, 2, block=64, config_id=142),
              dict(floor_mode=1, k_min_blocks=3)),
             ("3000 6/3 gamma VS", lambda: custom_config(3000, 6, 3, block=128, config_id=143), dict(vs_mode=1)),
-            ("8320 4/2 nb65", lambda: custom_config(8320, 4, 2, block=128, config_id=144), {})]
+            ("8320 4/2 nb65", lambda: custom_config(8320, 4, 2, block=128, config_id=144), {}),
+            ("4096 66/2 B64 nb64", lambda: custom_config(4096, 66, 2, block=64, config_id=145), {}),
+            ("8193 32/8 nb65", lambda: custom_config(8193, 32, 8, block=128, config_id=146), dict(floor_mode=1)),
+            ("16384 32/8 nb128", lambda: custom_config(16384, 32, 8, block=128, config_id=147), dict(vs_mode=1)),
+            ("16384 16/4 nb128", lambda: custom_config(16384, 16, 4, block=128, config_id=148), {}),
+            ("33000 4/2 nb258", lambda: custom_config(33000, 4, 2, block=128, config_id=149), {})]
 
 
 @pytest.mark.parametrize("name,make_cfg,kw", _stagewise_cases(), ids=[c[0] for c in _stagewise_cases()])
 def test_prefill_lists_match_stagewise(name, make_cfg, kw):
-    """crisp_prefill_attn with caller lists reproduces the stage-by-stage calls exactly, on
-    either side of the short-layer selection's 64 blocks."""
+    """crisp_prefill_attn with caller lists reproduces the stage-by-stage calls exactly, for every
+    division of the work between the estimator and the selection."""
     C = _crisp()
     _say(f"prefill lists == stages: {name}")
     cfg = make_cfg()
