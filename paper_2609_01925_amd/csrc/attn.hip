@@ -48,7 +48,7 @@
 // (2k-4k layers of 32 heads 11-12% faster than the persistent grid with split rows, 8k
 // 3-10% faster, 16k 14% slower).  With fewer units (few heads) the persistent grid takes
 // items i, i + grid, ... of that list and splits long rows; so does a longer layer with units
-// for at most half of that grid, whose pops would meet on one counter.
+// for at most half of that grid (of one KV group: somewhat more), whose pops would meet on one counter.
 #include <atomic>
 #include <type_traits>
 
@@ -72,7 +72,7 @@ struct Tile {
 constexpr float kSumLimit = 256.0f;          // a lane's tile sum of P above this forces a rescale
 constexpr int kCostBuckets = 8192;
 constexpr int kOneShotMinLen = 1 << 19;  // from this length on, sparse lists run one unit per workgroup
-constexpr int kStaticListMaxLen = 8192;  // up to this length (and with few units) items come from one list by workgroup index
+constexpr int kStaticListMaxLen = 8192;  // up to this length (and with few units) items come from one list, by index
 constexpr int kOneGroupListMaxLen = 16384;  // up to this length layers of one KV group do so with more units
 // Shortest chunk of a split row, in list entries: shorter ones cost more in partial results
 // (66 KB each way) than the shorter critical path saves (attention at 4k tokens, 8 heads:
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(Geo<BQ>::kThreads, Geo<BQ>::kWavesPerEU) void attn_
   for (;;) {
     __syncthreads();  // the previous unit is done with LDS and the unit slot
     if (a.static_list) {
-      // Short layers: items i, i + grid, ... of one longest-first list, no atomic (with one
+      // Short layers and few units: items i, i + grid, ... of one longest-first list, no atomic (with one
       // unit per workgroup, item i alone; the workgroups start in index order).  On a
       // persistent grid the pop's atomic and the wait for it cost about as much as a unit's
       // tiles, and a fixed stride balances as well (each round of grid items is no longer
@@ -901,14 +901,15 @@ __device__ __forceinline__ void for_units(const AttnArgs& a, int total, int tid,
   }
 }
 
-// The work-list builder.  It is one workgroup and runs once, so latency and instruction fetch bound it,
-// not work: up to kLenCache units the row lengths are read once (in batches of eight loads) and kept in
-// LDS, and the passes are rolled loops over them.  Larger layers read them again in each pass, by
-// for_units, which stands unrolled in every pass beside the loop and makes up most of the kernel's code
-// (128k tokens, 32 heads 66 us and 512k, 28 heads 180 us either way, of 43 and 600 ms).  Kernel time with lengths re-read from memory or held
-// in registers by unrolled passes -> now: 20k tokens, 32 heads 15.6 -> 12.6 us; 32k, 64-row
-// blocks 31.6 -> 27.3; 8k 8.5 -> 7.4; 2k 5.9 -> 4.6.  (All passes unrolled over registers
-// with the atomics of equal keys combined per wave: 22.8, 42, 9.0 and 8.3 us.)
+// The work-list builder.  It is one workgroup and runs once, so latency and instruction fetch
+// bound it, not work: up to kLenCache units the row lengths are read once (in batches of eight
+// loads) and kept in LDS, and the passes are rolled loops over them.  Kernel time with lengths
+// re-read from memory or held in registers by unrolled passes -> now: 20k tokens, 32 heads 15.6 ->
+// 12.6 us; 32k, 64-row blocks 31.6 -> 27.3; 8k 8.5 -> 7.4; 2k 5.9 -> 4.6.  (All passes unrolled over
+// registers with the atomics of equal keys combined per wave: 22.8, 42, 9.0 and 8.3 us.)  Larger
+// layers read the lengths again in each pass, by for_units, which stands unrolled in every pass
+// beside its loop and makes up most of the kernel's code (128k tokens, 32 heads 66 us and 512k, 28
+// heads 180 us before and now, of 43 and 600 ms).
 constexpr int kLenCache = 16384;  // rows whose lengths are kept in LDS between the passes
 __global__ __launch_bounds__(1024) void attn_schedule(AttnArgs a) {
   __shared__ int hist[kCostBuckets];
