@@ -1331,9 +1331,9 @@ __device__ void mid_vs_dir(const SelArgs& a, const float* P, uint8_t* m, uint8_t
 // the route, the selection and the lists of one head in one workgroup.  A head's causal
 // triangle fits LDS (at most 131 KB), so the row softmax, the radix passes, the counts and
 // the lists work on it there, and seven launches (each about 4.7 us however little it does)
-// become one: at 79 blocks (5k tokens, 64-row blocks) 40 us of launches -> 18.8 us, at 157
-// blocks (20k tokens) 47 -> 33.0.  It is bound by latency: rows and blocks are read four at a
-// time per wave.  The arithmetic and its order are those of sel_pe_softmax and of the separate
+// become one: at 79 blocks (5k tokens, 64-row blocks) 40 us of launches -> 18.4 us, at 157
+// blocks (20k tokens) 47 -> 32.0.  It is bound by latency: rows and blocks are read four at a
+// time per wave (a row's masks and scores one at a time: 19.3 and 33.4 us).  The arithmetic and its order are those of sel_pe_softmax and of the separate
 // launches, so the lists are the same.  grid hq, 1024 threads, one workgroup per CU.
 struct MidShared {
   float at[kMidBlocks * (kMidBlocks + 1) / 2];  // the head's pooled scores, row qb at qb (qb + 1) / 2
